@@ -117,8 +117,8 @@ def settle_steps(cfg):
     return max(2 * int(cfg["delay_max"]), int(round(SETTLE_MS / cfg["dt_ms"])))
 
 
-STEP_SOURCES = ("spk_internal.h", "spk_dev.h", "spk_step.hip", "spk_run.hip", "spk_run_batch.hip", "spk_proc.hip",
-                "spk_runtime.hip")
+STEP_SOURCES = ("spk_internal.h", "spk_dev.h", "spk_step.hip", "spk_run.hip", "spk_run_batch.hip", "spk_ring.hip",
+                "spk_proc.hip", "spk_runtime.hip")
 
 
 def step_source_sha():

@@ -92,7 +92,11 @@ enum { SPK_FORMAT_AUTO = 0, SPK_FORMAT_FULL = 1, SPK_FORMAT_COMPACT = 2, SPK_FOR
  * keeps the neuron state in LDS and hands each step over through barriers
  * inside the kernel; it needs one tile per compute unit or fewer (n <= 2^21
  * on MI355X), direct delivery with a single delay, or binned delivery with
- * delay_max * tiles / 8 <= 2048.  AUTO takes PERSISTENT where it applies and
+ * delay_max * tiles / 8 <= 2048.  Where a tile's inputs of every step up to the
+ * longest delay fit in its LDS (AUTO delivery, or DIRECT with one delay), the
+ * launch keeps them there and files events without pages, one workgroup per
+ * tile; calls of a few steps are then ordinary launches.  AUTO takes
+ * PERSISTENT where it applies and
  * the device runs it (checked once at creation), else GRAPH; asking for
  * PERSISTENT where it does not apply is SPK_EINVAL at creation. */
 enum { SPK_STEP_AUTO = 0, SPK_STEP_GRAPH = 1, SPK_STEP_PERSISTENT = 2 };
@@ -132,6 +136,8 @@ enum { SPK_STEP_AUTO = 0, SPK_STEP_GRAPH = 1, SPK_STEP_PERSISTENT = 2 };
  *   page of binned delivery (default: an equal share of 2 GiB);
  *   SPK_BATCH_STEPS caps the
  *   steps per batch (1..16, default 8; spk_stats_t.batch_steps);
+ *   SPK_RING=0 leaves out the steps with every pending input in LDS
+ *   (spk_params.step_mode) and their tiling;
  *   SPK_GEN_KEYS=0 makes the Bernoulli generator draw every row a second
  *   time to place it instead of keeping the first pass's synapses (the
  *   results are the same). */

@@ -179,6 +179,7 @@ struct StepArgs {
     const uint32_t *syn32;       // compact: class << 30 | j << 24 | target
     const RowDesc *desc;         // binned: n
     const uint16_t *toff;        // direct: T + 1 per row
+    uint32_t row_len;            // every row has this many synapses (0: lengths differ)
     const uint32_t *outdeg;      // n
     float *V;                    // n
     uint8_t *ref;                // n
@@ -252,6 +253,33 @@ struct RunArgs {
     uint64_t t0, n_steps;   // steps [t0, t0 + n_steps)
     uint32_t R;             // workgroups per XCD
     uint32_t D;             // binned delivery: steps per batch (1 .. min(d_min, kRunMaxD))
+};
+
+// Resident step kernel (spk_ring.hip): one workgroup per tile, the inputs of
+// every pending arrival step in LDS.
+constexpr uint32_t kRingBytes = 120u << 10;  // LDS for the pending inputs of a tile
+constexpr uint32_t kRingMaxT = 256;          // tiles
+constexpr uint32_t kRingBoxStride = 512;     // 8-byte words between mailboxes (4 KB, as the tile progress words)
+struct RingCtl {
+    uint64_t box[2][kRingMaxT * kRingBoxStride];  // per batch parity and tile
+    uint32_t abort_flag, pad[kCtlStride - 1];
+};
+struct RingArgs {
+    StepArgs s;
+    RingCtl *ctl;
+    void *ring;             // Tn * pslots * W accumulators: the pending inputs between launches
+    uint32_t *seg;          // 2 * Tn * seg_cap spikes, per batch parity and tile
+    uint32_t *cnts;         // 2 * kRunMaxD * Tn spike counts (raster of batches of several steps)
+    uint64_t t0, n_steps;
+    uint32_t Tn;            // tiles that hold neurons
+    uint32_t D;             // steps per batch
+    uint32_t seg_cap;
+    uint32_t e0;            // batches published before this launch
+    uint32_t counts;        // accumulators are packed event counts
+    double w0, w1;          // ... fp32 mode: the two classes' units times 2^-shift64
+    uint32_t pending;       // steps of the last launch's last batch, if its gather was left to this one
+    uint32_t defer;         // leave the gather of the last batch to the next launch
+    uint32_t waits;         // tiles wait for each other inside the launch (it is cooperative)
 };
 
 // spk_gen.hip -- connectivity expansion
@@ -334,5 +362,10 @@ bool run_supported(const StepArgs &a, uint32_t R);
 bool run_batch_supported(const StepArgs &a, uint32_t D);  // steps per batch D is valid for this network
 hipError_t launch_run(const RunArgs &ra, hipStream_t s);
 hipError_t launch_run_batched(const RunArgs &ra, hipStream_t s);  // spk_run_batch.hip
+
+// spk_ring.hip -- the resident step kernel
+uint32_t ring_acc_bytes(bool fixed, bool counts);
+bool ring_supported(const RingArgs &ra);
+hipError_t launch_ring(const RingArgs &ra, hipStream_t s);
 
 }  // namespace spk

@@ -58,6 +58,7 @@ constexpr uint32_t kBatch = 32;                    // steps per captured graph
 constexpr uint64_t kPageBudget = 256ull << 20;     // page records across all pages (2 GiB)
 constexpr uint64_t kDebugPageCap = 4096;           // records per page for spk_debug_deliver
 constexpr uint64_t kRunMaxSteps = 1ull << 24;      // steps per persistent launch (barrier epochs fit u32)
+constexpr uint64_t kRingPlainBatches = 3;          // batches of a call launched one by one (resident kernel)
 constexpr uint32_t kFlagRunStopped = 4u;           // device flag: a persistent launch stopped early
 
 // Scratch of spk_deliver_noalloc: one fixed area per device, held until the
@@ -144,26 +145,33 @@ bool quantise(float w, int S, int32_t *out)
 // Tiles of W neurons (a power of two, at most kMaxTileW), 8 groups of T8
 // tiles; the smallest W that keeps T8 <= max_t8 (default 32: one tile per
 // compute unit).  SPK_TILES_PER_XCD overrides max_t8 (a tuning knob).
-Tiling make_tiling(uint32_t n)
+Tiling tiling_of(uint32_t n, uint32_t W)
 {
-    uint32_t max_t8 = 32;
-    if (const char *e = std::getenv("SPK_TILES_PER_XCD")) {
-        const long v = std::strtol(e, nullptr, 10);
-        if (v >= 1 && v <= (long)kMaxT8) max_t8 = (uint32_t)v;
-    }
     Tiling tl{};
-    uint32_t W = 64, logW = 6;
-    while (W < kMaxTileW && (n + 8ull * W - 1) / (8ull * W) > max_t8) {
-        W <<= 1;
-        logW++;
-    }
     tl.W = W;
-    tl.logW = logW;
+    while ((1u << tl.logW) < W) tl.logW++;
     tl.T8 = (uint32_t)((n + 8ull * W - 1) / (8ull * W));
     tl.T = kGroups * tl.T8;
     tl.Gw = tl.T8 * W;
     tl.T8inv = tl.T8 > 1 ? (uint32_t)(((1ull << 32) + tl.T8 - 1) / tl.T8) : 0u;
     return tl;
+}
+
+uint32_t tiles_per_xcd_cap()
+{
+    if (const char *e = std::getenv("SPK_TILES_PER_XCD")) {
+        const long v = std::strtol(e, nullptr, 10);
+        if (v >= 1 && v <= (long)kMaxT8) return (uint32_t)v;
+    }
+    return 32;
+}
+
+Tiling make_tiling(uint32_t n)
+{
+    const uint32_t max_t8 = tiles_per_xcd_cap();
+    uint32_t W = 64;
+    while (W < kMaxTileW && (n + 8ull * W - 1) / (8ull * W) > max_t8) W <<= 1;
+    return tiling_of(n, W);
 }
 
 }  // namespace
@@ -221,6 +229,16 @@ struct spk_net {
     uint32_t run_R = 0;
     uint32_t run_D = 1;  // persistent kernel, binned delivery: steps per batch
     RunCtl *ctl = nullptr;
+    // resident step kernel: planned before the rows are laid out (the tiling
+    // and the per-tile row offsets depend on it), used if it can be launched
+    bool ring = false;
+    bool ring_counts = false;   // accumulators are packed event counts
+    uint32_t ring_epoch = 0;    // batches published so far
+    uint32_t ring_pending = 0;  // steps of the last batch, if its spikes are still to be gathered
+    uint32_t seg_cap = 0;
+    RingCtl *rctl = nullptr;
+    void *ring_buf = nullptr;
+    uint32_t *ring_seg = nullptr, *ring_cnts = nullptr;
     // profiling
     bool profiling = false;
     std::vector<hipEvent_t> ev_free;
@@ -335,6 +353,7 @@ StepArgs step_args(const spk_net *net)
     a.syn32 = net->syn32;
     a.desc = net->desc;
     a.toff = net->toff;
+    a.row_len = net->P.conn_kind == SPK_CONN_FIXED_OUT ? net->P.k_out : 0u;
     a.outdeg = net->outdeg;
     a.V = net->V;
     a.ref = net->ref;
@@ -522,6 +541,80 @@ void class_units(spk_net *net)
     }
 }
 
+// Whether the resident step kernel serves the network, and its tiling
+// (called once the synapse format is known, before rows are laid out).
+// in_max: the largest in-degree per class where it is known (explicit
+// adjacency), else null.
+void plan_ring(spk_net *net, uint64_t nnz_expected, const uint64_t *in_max)
+{
+    net->ring = net->ring_counts = false;
+    const spk_params &P = net->P;
+    if (net->proc || P.step_mode == SPK_STEP_GRAPH || P.delivery == SPK_DELIVERY_BINNED) return;
+    if (P.delivery == SPK_DELIVERY_DIRECT && net->lists > 1) return;
+    if (const char *e = std::getenv("SPK_RING"))
+        if (e[0] == '0') return;
+    const double n = (double)net->n, ne = (double)net->n_exc, ni = n - ne;
+    // Packed counts: at most two classes, and no neuron may receive 2^16
+    // events of one class in one step (each in-synapse delivers at most one).
+    // Checked against the range pass once it has run (finish_rows); here
+    // only where that check is sure to hold.
+    bool counts = net->compact && net->n_cls <= 2;
+    if (counts) {
+        const double a0 = (double)net->ctab.abs[0], a1 = (double)net->ctab.abs[1];
+        if (in_max) {
+            counts = in_max[0] < 65536 && in_max[1] < 65536;
+        } else {
+            const double per = (double)nnz_expected / n / n;  // synapses per (source, target)
+            double me = ne * per, mi = ni * per;
+            if (P.conn_kind == SPK_CONN_FIXED_IN) {
+                me = P.k_in_exc;
+                mi = P.k_in_inh;
+            }
+            const double sum = (me + 12.0 * std::sqrt(me) + 64.0) * a0 + (mi + 12.0 * std::sqrt(mi) + 64.0) * a1;
+            counts = a0 > 0 && a1 > 0 && sum / std::min(a0, a1) < 65000.0;
+        }
+    }
+    if (!counts && net->lists > 1) return;
+    const uint32_t acc = ring_acc_bytes(P.acc_mode == SPK_ACC_FIXED, counts);
+    // Tile width (microseconds per step on one MI355X):
+    //   one tile of up to 2,048 neurons has no hand-off: 1,000 neurons 2.5
+    //   against 3.8 on two tiles, 2,000 with fan-out 100 2.8 against 3.6; with
+    //   fan-out 1,000 one compute unit is slower at the events, 4.5 against
+    //   3.8 on four (2e6 synapses), hence the bound on the synapses;
+    //   512 neurons per tile rather than fewer: half the lanes idle in the
+    //   update costs less than more mailboxes to poll (30,000 neurons 4.8 at
+    //   512, 5.2 at 256, 6.6 at 128, 4.9 at 1,024);
+    //   at most 128 tiles (120,000 neurons: 6.2 on 118 tiles of 1,024, 7.0 on
+    //   235 of 512), but not wider than 2,048 for it (300,000: 7.9 on 147
+    //   tiles of 2,048, 8.6 on 74 of 4,096);
+    //   from 4e8 synapses on the gather decides, on as many compute units as
+    //   there are (250,000 neurons, 1.25e9 synapses: 8.8 on 245 tiles, 10.0
+    //   on 123; delay 15 and 1e9 synapses: 2.0 on 196, 2.6 on 98).
+    const uint64_t nnz = nnz_expected;
+    const bool fixed_cap = std::getenv("SPK_TILES_PER_XCD") != nullptr;
+    auto fits = [&](uint32_t W) { return (uint64_t)net->dmax * W * acc <= kRingBytes; };
+    auto tiles = [&](uint32_t W) { return (net->n + W - 1) / W; };
+    uint32_t W = 0;
+    if (fixed_cap) {
+        W = make_tiling(net->n).W;
+    } else if (net->n <= 2048 && nnz <= (1u << 20) && fits(net->n <= 1024 ? 1024 : 2048)) {
+        W = net->n <= 1024 ? 1024 : 2048;
+    } else {
+        const uint32_t most = nnz >= 400000000ull ? kRingMaxT : 128;
+        for (W = 512; W < kMaxTileW; W <<= 1)
+            if (tiles(W) <= most || (W >= 2048 && tiles(W) <= kRingMaxT)) break;
+        while (W > 64 && !fits(W)) W >>= 1;  // (narrower tiles hold more arrival steps)
+    }
+    if (!fits(W)) return;
+    const Tiling tl = tiling_of(net->n, W);
+    if (tl.T > kRingMaxT) return;
+    // the rows' tile offsets: 64 MB, or half the full synapses' size
+    if ((double)net->n * (tl.T + 1) * 2.0 > std::max(64e6, 4.0 * (double)nnz)) return;
+    net->ring = true;
+    net->ring_counts = counts;
+    net->tl = tl;
+}
+
 // Synapse storage of the chosen format.
 spk_status alloc_syn(spk_net *net, void **p, uint64_t nnz)
 {
@@ -603,6 +696,11 @@ spk_status derive(spk_net *net, bool explicit_csr)
     if (!explicit_csr) {  // population weights: class 0 excitatory, 1 inhibitory
         const float w[2] = {P.w_exc, P.w_inh};
         SPK_TRY(choose_format(net, P.w_uniform ? nullptr : w, 2));
+        const double nn = (double)P.n;
+        plan_ring(net, (uint64_t)(P.conn_kind == SPK_CONN_BERNOULLI ? nn * nn * P.p
+                                  : P.conn_kind == SPK_CONN_FIXED_OUT ? nn * P.k_out
+                                                                      : nn * ((double)P.k_in_exc + P.k_in_inh)),
+                  nullptr);
     }
     const uint64_t seed = P.seed;
     net->keys.conn = stream_key(seed, TAG_CONN);
@@ -684,6 +782,7 @@ spk_status choose_delivery(spk_net *net, RowIndex *ix)
                                     "XCD group; use fewer delays or direct delivery");
         direct = false;
     }
+    if (net->ring) direct = true;  // (its rows are read by tile)
     net->direct = direct;
     *ix = RowIndex{};
     if (direct) {
@@ -775,13 +874,20 @@ spk_status finish_rows(spk_net *net)
         net->shift64 = std::max(0, std::min(100, 52 - e));
     }
     class_units(net);
+    if (net->ring_counts && net->P.conn_kind != SPK_CONN_EXPLICIT &&
+        (m / std::max<uint64_t>(1, std::min(net->ctab.abs[0], net->ctab.abs[1])) > 65535 ||
+         !net->ctab.abs[0] || !net->ctab.abs[1])) {
+        // a neuron could receive 2^16 events of a class: sums, where they fit
+        net->ring_counts = false;
+        if (net->lists > 1 || (uint64_t)net->dmax * net->tl.W * ring_acc_bytes(fixed, false) > kRingBytes) net->ring = false;
+    }
 
     // Steps per batch of the persistent kernel (binned delivery): up
     // to the smallest delay, so that nothing a batch files arrives within it,
     // and within the bucket, slot and LDS limits.
     const Tiling &tl = net->tl;
     net->run_D = 1;
-    if (!net->direct) {
+    if (!net->direct || (net->ring && net->P.delivery != SPK_DELIVERY_DIRECT)) {
         // Default at most 8 steps: longer batches save hand-offs but give a
         // push block more events than one 16K-event sorting window holds
         // (measured on the delay-15 network: 7.3 us per step at 8, 7.4 at
@@ -793,7 +899,7 @@ spk_status finish_rows(spk_net *net)
         }
         uint32_t D = std::min<uint32_t>(net->dmin, cap);
         // the tile keeps one accumulator array per step of the batch in LDS
-        while (D > 1 && ((uint64_t)(D + net->lists - 1) * tl.T8 > kRunMaxBuckets || D * tl.W > kMaxTileW)) D--;
+        while (D > 1 && ((!net->ring && (uint64_t)(D + net->lists - 1) * tl.T8 > kRunMaxBuckets) || D * tl.W > kMaxTileW)) D--;
         net->run_D = D;
     }
     // Spike lists: direct delivery reads the lists of steps t - dmax .. t - dmin
@@ -802,6 +908,7 @@ spk_status finish_rows(spk_net *net)
     // still reads t, so there are three; with batches of
     // D steps, one XCD may publish the next batch while another reads this one.
     net->spk_slots = net->direct ? net->dmax + 1 : std::max<uint32_t>(3, 2 * net->run_D);
+    if (net->ring) net->pslots = net->dmax;
     if (!net->direct) {
         // Pages: (group, push block, arrival slot, tile).  A page never holds
         // more than nnz records (each synapse arrives at most once per slot),
@@ -1004,10 +1111,58 @@ RunArgs run_args(const spk_net *net, uint64_t t0, uint64_t n_steps)
     return ra;
 }
 
-hipError_t launch_persistent(const spk_net *net, const RunArgs &ra, hipStream_t s)
+RingArgs ring_args(const spk_net *net, uint64_t t0, uint64_t n_steps)
 {
-    (void)net;
-    return launch_run(ra, s);
+    RingArgs ra{};
+    ra.s = step_args(net);
+    ra.ctl = net->rctl;
+    ra.ring = net->ring_buf;
+    ra.seg = net->ring_seg;
+    ra.cnts = net->ring_cnts;
+    ra.t0 = t0;
+    ra.n_steps = n_steps;
+    ra.Tn = (net->n + net->tl.W - 1) / net->tl.W;
+    ra.D = net->run_D;
+    ra.seg_cap = net->seg_cap;
+    ra.e0 = net->ring_epoch;
+    ra.counts = net->ring_counts ? 1u : 0u;
+    ra.w0 = std::ldexp((double)net->wval[0], -net->shift64);
+    ra.w1 = std::ldexp((double)net->wval[1], -net->shift64);
+    ra.pending = net->ring_pending;
+    // the raster positions of a batch need every tile's count, so a recorded
+    // run waits for its last batch too
+    ra.defer = ra.Tn > 1 && !net->P.raster_capacity ? 1u : 0u;
+    ra.waits = ra.Tn > 1 && (n_steps == 0 || n_steps > ra.D || !ra.defer) ? 1u : 0u;
+    return ra;
+}
+
+hipError_t launch_persistent(spk_net *net, uint64_t t0, uint64_t n_steps, hipStream_t s)
+{
+    if (net->ring) {
+        // A few batches are launched one by one: such a launch waits for
+        // nothing inside and is an ordinary one.
+        const uint64_t D = net->run_D;
+        const bool single = n_steps > 0 && n_steps <= kRingPlainBatches * D && !net->P.raster_capacity;
+        do {
+            const uint64_t B = single ? std::min<uint64_t>(D, n_steps) : n_steps;
+            const RingArgs ra = ring_args(net, t0, B);
+            const hipError_t e = launch_ring(ra, s);
+            if (e != hipSuccess) return e;
+            net->ring_epoch += (uint32_t)((B + D - 1) / D);
+            if (B) net->ring_pending = ra.defer ? (uint32_t)((B - 1) % D + 1) : 0u;
+            t0 += B;
+            n_steps -= B;
+        } while (n_steps);
+        return hipSuccess;
+    }
+    return launch_run(run_args(net, t0, n_steps), s);
+}
+
+// The control words of the next launch start at zero (the resident kernel's
+// carry on from launch to launch).
+hipError_t reset_control(const spk_net *net, hipStream_t s)
+{
+    return net->ring ? hipSuccess : hipMemsetAsync(net->ctl, 0, sizeof(RunCtl), s);
 }
 
 // A zero-step launch of the persistent kernel: checks that the workgroups
@@ -1016,11 +1171,12 @@ spk_status probe_persistent(spk_net *net, bool *ok)
 {
     hipStream_t s = net->stream;
     *ok = false;
-    SPK_HIP(hipMemsetAsync(net->ctl, 0, sizeof(RunCtl), s));
-    hipError_t e = launch_persistent(net, run_args(net, net->t, 0), s);
+    hipError_t e = reset_control(net, s);
+    if (e == hipSuccess) e = launch_persistent(net, net->t, 0, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     uint32_t abort_flag = 1;
-    if (e == hipSuccess) e = hipMemcpy(&abort_flag, &net->ctl->abort_flag, 4, hipMemcpyDeviceToHost);
+    const uint32_t *af = net->ring ? &net->rctl->abort_flag : &net->ctl->abort_flag;
+    if (e == hipSuccess) e = hipMemcpy(&abort_flag, af, 4, hipMemcpyDeviceToHost);
     if (e == hipSuccess && abort_flag == 0) {
         *ok = true;
         return SPK_OK;
@@ -1044,6 +1200,28 @@ spk_status choose_step_mode(spk_net *net)
     SPK_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, net->device));
     const int cus = cu_count();
     net->run_R = cus > 0 && cus % (int)kGroups == 0 ? (uint32_t)(cus / (int)kGroups) : 0u;
+    if (net->ring) {
+        // one workgroup per tile, all resident at once
+        const Tiling &tl = net->tl;
+        const uint32_t Tn = (net->n + tl.W - 1) / tl.W;
+        const size_t bytes = (size_t)Tn * net->pslots * tl.W * ring_acc_bytes(net->P.acc_mode == SPK_ACC_FIXED, net->ring_counts);
+        net->seg_cap = net->run_D * tl.W;
+        bool ok = (Tn == 1 || (coop && (int)tl.T <= cus)) && ring_supported(ring_args(net, 0, 0));
+        if (ok) {
+            SPK_TRY(dalloc(net, (uint8_t **)&net->ring_buf, bytes));
+            SPK_TRY(dalloc(net, &net->ring_seg, (size_t)2 * Tn * net->seg_cap));
+            SPK_TRY(dalloc(net, &net->ring_cnts, (size_t)2 * kRunMaxD * Tn));
+            SPK_TRY(dalloc(net, &net->rctl, 1));
+            SPK_HIP(hipMemsetAsync(net->ring_buf, 0, bytes, net->stream));
+            SPK_HIP(hipMemsetAsync(net->rctl, 0, sizeof(RingCtl), net->stream));
+            SPK_TRY(probe_persistent(net, &ok));
+        }
+        if (ok) {
+            net->persistent = true;
+            return SPK_OK;
+        }
+        net->ring = false;  // (the rows serve direct delivery)
+    }
     const StepArgs a = step_args(net);
     const bool run_fits = coop && run_supported(a, net->run_R) && run_batch_supported(a, net->direct ? 1u : net->run_D);
     if (!run_fits) {
@@ -1307,8 +1485,20 @@ spk_status spk_create_from_csr(const spk_params *params, uint32_t n, const uint6
             SPK_TRY(choose_format(net, fits ? cls : nullptr,
                                   fits ? std::max<uint32_t>(1, (uint32_t)distinct.size()) : 0));
         }
+        // in-degrees per class, where the packed counts of the resident
+        // kernel could overflow
+        std::vector<uint32_t> indeg;
+        const bool want_in = net->compact && net->n_cls <= 2 && nnz > 65535;
+        if (want_in) indeg.assign((size_t)n * 2, 0);
+        uint32_t cls1 = 0;
+        if (net->n_cls == 2) std::memcpy(&cls1, &net->cls_w[1], 4);
         for (uint64_t e = 0; e < nnz; e++) {
             if (col[e] >= n) return fail(SPK_EINVAL, "target id out of range");
+            if (want_in) {
+                uint32_t b;
+                std::memcpy(&b, &w[e], 4);
+                indeg[2 * (size_t)col[e] + (net->n_cls == 2 && b == cls1)]++;
+            }
             const uint32_t d = delay ? delay[e] : net->P.delay_min;
             if (d < net->P.delay_min || d > net->P.delay_max)
                 return fail(SPK_EINVAL, "delay out of [delay_min, delay_max]");
@@ -1320,6 +1510,12 @@ spk_status spk_create_from_csr(const spk_params *params, uint32_t n, const uint6
         }
         net->nnz = nnz;
         net->max_row = (uint32_t)std::min<uint64_t>(max_row, 0xffffffffull);
+        uint64_t in_max[2] = {nnz, nnz};
+        if (want_in) {
+            in_max[0] = in_max[1] = 0;
+            for (size_t k = 0; k < indeg.size(); k++) in_max[k & 1] = std::max<uint64_t>(in_max[k & 1], indeg[k]);
+        }
+        plan_ring(net, nnz, in_max);
         SPK_TRY(setup_stream(net, stream));
         hipStream_t s = net->stream;
         RowIndex ix{};
@@ -1384,9 +1580,9 @@ spk_status spk_step(spk_net *net, uint64_t n_steps)
                 SPK_TRY(get_event(net, &e0));
                 SPK_TRY(get_event(net, &e1));
             }
-            SPK_HIP(hipMemsetAsync(net->ctl, 0, sizeof(RunCtl), s));
+            SPK_HIP(reset_control(net, s));
             if (e0) SPK_HIP(hipEventRecord(e0, s));
-            SPK_HIP(launch_persistent(net, run_args(net, net->t, B), s));
+            SPK_HIP(launch_persistent(net, net->t, B, s));
             if (e1) {
                 SPK_HIP(hipEventRecord(e1, s));
                 net->ev_run.push_back({e0, e1});
@@ -1463,6 +1659,16 @@ spk_status spk_read_delivered(spk_net *net, uint64_t t0, uint64_t n, uint64_t *o
     SPK_TRY(check_ready(net));
     if (t0 + n > net->P.max_steps || (n && !out)) return fail(SPK_EINVAL, "range");
     SPK_TRY(sync_flags(net, nullptr));
+    if (net->ring && net->lists == 1) {
+        // one delay: the events delivered at t are those emitted at t - dmin
+        for (uint64_t k = 0; k < n && t0 + k < net->dmin; k++) out[k] = 0;
+        const uint64_t skip = t0 < net->dmin ? std::min<uint64_t>(n, net->dmin - t0) : 0;
+        const uint64_t last = std::max<uint64_t>(net->t, t0 + skip);  // steps not run yet deliver nothing
+        const uint64_t m = std::min<uint64_t>(n - skip, last - (t0 + skip));
+        SPK_TRY(read_groups(net, net->events8, 8, t0 + skip - net->dmin, m, out + skip));
+        for (uint64_t k = skip + m; k < n; k++) out[k] = 0;
+        return SPK_OK;
+    }
     return read_groups(net, net->delivered8, 8, t0, n, out);
 }
 
@@ -1709,10 +1915,14 @@ spk_status spk_stats(spk_net *net, spk_stats_t *out)
     st.bytes_per_synapse = net->proc ? 0.0 : net->compact ? 4.0 : 8.0;
     st.tile_width = net->tl.W;
     st.tiles = net->tl.T;
-    st.delivery = net->direct ? SPK_DELIVERY_DIRECT : SPK_DELIVERY_BINNED;
+    // (the resident kernel files events by arrival step right after their
+    // spike, as binned delivery does; with one delay of one step, or where
+    // direct delivery was asked for, a tile reads the due rows)
+    const bool filed = net->ring && net->P.delivery != SPK_DELIVERY_DIRECT && net->dmax > 1;
+    st.delivery = net->direct && !filed ? SPK_DELIVERY_DIRECT : SPK_DELIVERY_BINNED;
     st.page_cap = net->page_cap;
     st.step_mode = net->persistent ? SPK_STEP_PERSISTENT : SPK_STEP_GRAPH;
-    st.batch_steps = net->persistent && !net->direct ? net->run_D : 1u;
+    st.batch_steps = net->persistent && (!net->direct || net->ring) ? net->run_D : 1u;
     st.setup_ms = net->setup_ms;
     st.gen_ms = net->gen_ms;
     st.range_ms = net->range_ms;

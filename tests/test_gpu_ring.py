@@ -1,0 +1,141 @@
+"""The resident step kernel (one workgroup per tile, every pending input in
+LDS) against the oracle and the other step paths, where it can go wrong: one
+tile and several, the edges of tiles and of the spike list, the mailbox's
+carried spikes, batches, calls whose last batch is gathered by the next one,
+and in-degrees beyond the packed event counts.  Fixed-point sums and fp32
+sums (exact integers rounded once) are compared bit for bit."""
+import os
+
+import numpy as np
+import pytest
+
+import inputs as I
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def spk():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2102_04681_amd import spk as mod
+    mod.lib()
+    return mod
+
+
+def _records(g, raster=True):
+    v, r = g.state()
+    out = [g.spike_counts(), g.events(), g.delivered(), v.view(np.uint32), r]
+    return out + list(g.raster()) if raster else out
+
+
+def _same(a, b, what):
+    for x, y, name in zip(a, b, ("counts", "events", "delivered", "v", "ref", "offsets", "ids")):
+        assert np.array_equal(x, y), f"{what}: {name}"
+
+
+def _burst(n, k_out, **over):
+    """Every neuron starts above threshold: all fire at the first step."""
+    return I.config(4, n=n, k_out=k_out, v0_lo=-49.0, v0_hi=-49.0, t_ref_ms=0.3, **over)
+
+
+CASES = [  # name, parameters, steps, tiles of the resident kernel
+    ("one", lambda: I.scaled(4, 1, k_out=1, delay_max=1), 20, 1),
+    ("1024", lambda: I.config(0, driven=True, n=1024), 120, 1),
+    ("1025", lambda: I.config(0, driven=True, n=1025), 120, 1),
+    ("2048", lambda: I.scaled(4, 2048, k_out=100, delay_max=7), 120, 1),
+    ("2049", lambda: I.scaled(4, 2049, k_out=100, delay_max=7), 120, 5),
+    ("one-tile-list", lambda: _burst(2047, 40, delay_max=5), 12, 1),         # 2,047 spikes in a list of 1,024
+    ("list", lambda: _burst(5000, 60, delay_max=5), 12, 10),                 # 5,000 in a list of 2,048
+    ("batches-burst", lambda: _burst(3000, 60, delay_min=4, delay_max=9), 21, 6),
+    ("batches-one-tile", lambda: I.scaled(4, 900, k_out=90, delay_min=3, delay_max=9), 100, 1),
+    ("in-degree", lambda: I.scaled(2, 6000, k_in_exc=480, k_in_inh=120), 120, 12),
+    ("sources", lambda: I.scaled(3, 9000, k_out=300), 60, 18),
+    ("bernoulli", lambda: I.scaled(1, 6000), 120, 12),
+    ("fanout-1", lambda: I.scaled(4, 3000, k_out=1, delay_max=3), 80, 6),
+]
+
+
+@pytest.mark.parametrize("name,mk,T,tiles", CASES, ids=[c[0] for c in CASES])
+@pytest.mark.parametrize("acc", [I.ACC_FIXED, I.ACC_F32], ids=["fixed", "f32"])
+def test_resident_kernel_bit_identical(spk, name, mk, T, tiles, acc):
+    cfg = dict(mk(), acc_mode=acc)
+    cap = cfg["n"] * T
+    g = spk.Net(cfg, max_steps=T, raster_capacity=cap)
+    st = g.stats()
+    assert st["step_mode"] == spk.SPK_STEP_PERSISTENT and st["page_cap"] == 0
+    assert -(-cfg["n"] // st["tile_width"]) == tiles
+    g.step(T // 3)
+    g.step(1)
+    g.step(T - T // 3 - 1)
+    got = _records(g)
+    if acc == I.ACC_FIXED:
+        o = oracle.Net(cfg)
+        r = o.run(T)
+        v, ref = o.state()
+        want = [r["counts"], r["events"], r["delivered"], v.view(np.uint32), ref, r["offs"], r["raster"]]
+    else:
+        h = spk.Net(dict(cfg, step_mode=1), max_steps=T, raster_capacity=cap)
+        h.step(T)
+        want = _records(h)
+    assert got[0].sum() > 0 or name == "one"
+    _same(got, want, name)
+    # without a raster a call leaves its last batch to the next one: calls of
+    # one step, of a few, of several batches
+    g = spk.Net(cfg, max_steps=T)
+    left = T
+    for k in (1, 1, 2, 7, 3, 1, 20, 5, 1, T):
+        k = min(k, left)
+        g.step(k)
+        left -= k
+    _same(_records(g, raster=False), want[:5], f"{name}, many calls")
+
+
+def test_resident_kernel_serves_one_delay_of_weights_per_synapse(spk):
+    cfg = I.scaled(3, 9000, k_out=300, delay_min=2, delay_max=2)
+    a, b = spk.Net(cfg, max_steps=50), spk.Net(dict(cfg, step_mode=1), max_steps=50)
+    for g in (a, b):
+        g.step(17)
+        g.step(33)
+    assert a.stats()["page_cap"] == 0 and a.stats()["step_mode"] == 2
+    _same(_records(a, raster=False), _records(b, raster=False), "d2")
+    # deliveries of steps not run yet read as 0
+    c = spk.Net(cfg, max_steps=50)
+    c.step(20)
+    assert not c.delivered(20, 30).any() and np.array_equal(c.delivered(0, 20), a.delivered(0, 20))
+
+
+@pytest.mark.parametrize("delays", [(1, 1), (1, 2)], ids=["one-delay", "two"])
+def test_in_degree_beyond_the_packed_counts(spk, delays):
+    # 80,000 synapses of one weight from two sources that fire together into
+    # neuron 5: more events in one step than a 16-bit count holds
+    n, m = 300, 40_000
+    row_ptr = np.zeros(n + 1, dtype=np.uint64)
+    row_ptr[1:] = np.minimum(np.arange(1, n + 1), 2) * m
+    col = np.full(2 * m, 5, dtype=np.uint32)
+    w = np.full(2 * m, 2.0 ** -14, dtype=np.float32)
+    d = np.full(2 * m, delays[0], dtype=np.uint8)
+    d[: m // 2] = delays[1]
+    cfg = I.explicit_params(n, v0_lo=-49.0, v0_hi=-49.0, t_ref_ms=5.0, delay_min=delays[0], delay_max=delays[1],
+                            acc_mode=I.ACC_FIXED)
+    g = spk.Net(cfg, max_steps=8, csr=(row_ptr, col, w, d))
+    o = oracle.Net(cfg, csr=(row_ptr, col, w, d))
+    g.step(8)
+    r = o.run(8)
+    v, ref = o.state()
+    _same(_records(g, raster=False), [r["counts"], r["events"], r["delivered"], v.view(np.uint32), ref], "hub")
+
+
+@pytest.mark.parametrize("mk", [lambda: I.scaled(4, 8000, k_out=300), lambda: I.scaled(1, 6000),
+                                lambda: I.scaled(4, 20000, k_out=50, delay_min=2, delay_max=8)],
+                         ids=["delays", "one-delay", "short-rows"])
+def test_resident_network_deliveries_match_oracle(spk, mk):
+    cfg = dict(mk(), acc_mode=I.ACC_FIXED)
+    g, o = spk.Net(cfg, max_steps=1), oracle.Net(cfg)
+    for count in (0, 1, 37, cfg["n"] // 3):
+        spikes = I.spike_set(cfg["n"], count, seed=count)
+        for delay in (0, cfg["delay_max"]):
+            want = o.deliver(spikes, delay=delay, fixed=True)[1]
+            assert np.array_equal(g.debug_deliver(spikes, delay=delay).astype(np.int64), want)
