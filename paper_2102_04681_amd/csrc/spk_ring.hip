@@ -18,16 +18,20 @@
 //   2. publication: a 16-byte mailbox per tile and batch parity holds the
 //      batch's stamp, the spike count and up to three spikes; more go to the
 //      tile's segment of the spike list (stored and waited for before the
-//      mailbox).  Both 8-byte halves carry the stamp, so neither needs an
-//      order between them;
-//   3. hand-off: four waves poll the mailboxes (agent-scope loads; the data
-//      crosses XCDs) while all threads draw the next batch's external input
-//      a unit at a time between looks;
-//   4. gather: the spikes as one list in LDS, shared among the 16 waves.
-//      Lane l of a wave resolves spike l (one unaligned 4-byte load gives
-//      the run's two ends); the wave's runs are then walked 64 records at a
-//      time, the record's run found from a bit mask of run starts by a
-//      population count instead of a search.
+//      mailbox).  Both 8-byte words carry the stamp, so they need no order
+//      between them;
+//   3. hand-off: wave w polls the mailboxes of tiles w, w + 16, ... itself
+//      (agent-scope loads; the data crosses XCDs), drawing the next batch's
+//      external input a unit at a time between looks (draws are private to
+//      a thread).  No barrier, list or prefix stands between a mailbox and
+//      its gather: lane l of the wave holds the mailbox of tile l / LP and
+//      takes its spikes l % LP, l % LP + LP, ... (LP = 64 / tiles per wave;
+//      with fewer than 16 tiles several waves share a tile's spikes);
+//   4. gather: the lane resolves its spike's run (one unaligned 4-byte load
+//      gives the run's two ends, the next spike's in flight meanwhile); the
+//      wave's runs are then walked 64 records at a time, the record's run
+//      found from a bit mask of run starts by a population count instead of
+//      a search.
 //
 // The gather of a launch's last batch may be left to the next launch (defer,
 // pending): the spikes stay in the mailboxes and segments of their parity.  A
@@ -58,8 +62,8 @@ namespace {
 
 constexpr uint32_t kRT = 1024;                        // threads
 constexpr uint32_t kRW = kRT / kWave;                 // waves
-constexpr uint32_t kList = 2048;                      // spikes gathered at once
-constexpr uint32_t kList1 = kList / 2;                // ... of a network of one tile (8-byte entries)
+constexpr uint32_t kList1 = 1024;                     // one tile: spikes gathered at once
+constexpr int kMany = 4;                              // runs per lane walked together, where there are many
 constexpr int kWin = 8;                               // 64-record windows in flight per wave
 constexpr uint64_t kTicks = 10ull * 100000000ull;     // 10 s of the 100 MHz clock
 constexpr uint32_t kStopped = 4u;                     // the network's device flag: a launch stopped early
@@ -68,11 +72,14 @@ constexpr uint32_t kIdBits = 28;                      // step of the batch << 24
 constexpr uint64_t kIdMask = (1ull << kIdBits) - 1;
 constexpr uint64_t kBegMask = (1ull << 48) - 1;
 static_assert(kRT == kBlockThreads, "the block-wide helpers assume workgroups of kBlockThreads");
-static_assert(kRingMaxT <= 4 * kWave, "four polling waves");
+static_assert(kRingMaxT <= kRW * 16, "a wave serves at most 16 tiles, four lanes each");
 
-// Mailbox halves.  a: spike 0 << 36 | count << 18 | 18-bit stamp (count <=
-// kMaxTileW < 2^14 ... 2^18); b: spike 2 << 36 | spike 1 << 8 | 8-bit stamp.
-// The same parity's stamps differ by 2 from batch to batch.
+// Mailbox words.  a: spike 0 << 36 | count << 18 | 18-bit stamp (count <=
+// kMaxTileW); b: spike 2 << 36 | spike 1 << 8 | 8-bit stamp.  The same
+// parity's stamps differ by 2 from batch to batch.
+struct Box {
+    uint64_t a, b;
+};
 __device__ __forceinline__ uint64_t box_a(uint32_t e, uint32_t cnt, uint32_t s0)
 {
     return (uint64_t)s0 << 36 | (uint64_t)cnt << 18 | (e & 0x3ffffu);
@@ -81,12 +88,16 @@ __device__ __forceinline__ uint64_t box_b(uint32_t e, uint32_t s1, uint32_t s2)
 {
     return (uint64_t)s2 << 36 | (uint64_t)s1 << 8 | (e & 0xffu);
 }
-__device__ __forceinline__ uint32_t box_cnt(uint64_t a) { return (uint32_t)(a >> 18) & 0x3ffffu; }
-__device__ __forceinline__ bool box_ready(uint64_t a, uint64_t b, uint32_t e)
+__device__ __forceinline__ uint32_t box_cnt(Box x) { return (uint32_t)(x.a >> 18) & 0x3ffffu; }
+// Spike i < kInline of a mailbox.
+__device__ __forceinline__ uint32_t box_spike(Box x, uint32_t i)
 {
-    if (((uint32_t)a & 0x3ffffu) != (e & 0x3ffffu)) return false;
-    const uint32_t c = box_cnt(a);
-    return c < 2 || c > kInline || ((uint32_t)b & 0xffu) == (e & 0xffu);
+    return i == 0 ? (uint32_t)(x.a >> 36) : i == 1 ? (uint32_t)(x.b >> 8) & (uint32_t)kIdMask : (uint32_t)(x.b >> 36);
+}
+__device__ __forceinline__ bool box_ready(Box x, uint32_t e)
+{
+    const uint32_t c = box_cnt(x);  // (a word that carries none of the c spikes need not have arrived)
+    return ((uint32_t)x.a & 0x3ffffu) == (e & 0x3ffffu) && (c < 2 || c > kInline || ((uint32_t)x.b & 0xffu) == (e & 0xffu));
 }
 
 __device__ __forceinline__ uint64_t ld_ag64(const uint64_t *p)
@@ -97,27 +108,37 @@ __device__ __forceinline__ void st_ag64(uint64_t *p, uint64_t v)
 {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Both words of mailbox k in one 16-byte load at agent scope (sc1; volatile:
+// polled in loops).  The load need not be atomic: each word is checked on its
+// own.  One request per mailbox and look instead of two took 250,000 neurons
+// from 9.5 to 9.3 us per step, four instead of two had cost 1.7: the looks of
+// every workgroup queue.
+__device__ __forceinline__ Box box_load(const uint64_t *boxes, uint32_t k)
+{
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)boxes, 0, kRingBoxBytes, 0x00027000);
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(k * kRingBoxStride * 8), 0, (int)(0x80000000u | 16u));
+    return Box{(uint64_t)v.y << 32 | v.x, (uint64_t)v.w << 32 | v.z};
+}
 
 // Accumulators of a variant: packed event counts (CNT), or sums.
 template <bool FIXED, bool CNT> struct RingAcc { using T = typename Acc<FIXED>::T; };
 template <bool FIXED> struct RingAcc<FIXED, true> { using T = uint32_t; };
 
-template <bool FIXED, bool CNT>
+template <bool FIXED, bool CNT, bool MULTI>
 struct RingLDS {
     using AccT = typename RingAcc<FIXED, CNT>::T;
-    AccT ring[kRingBytes / sizeof(AccT)];  // input of (arrival slot, neuron of the tile)
+    static constexpr uint32_t kBytes = MULTI ? kRingBytes : kRingBytes1;
+    AccT ring[kBytes / sizeof(AccT)];      // input of (arrival slot, neuron of the tile)
     uint8_t kp[kMaxTileW];                 // Poisson counts of step u of the batch at u * W
     uint64_t pois[256];
     uint16_t guide[256];
-    union {
-        uint32_t list[kList];              // spikes being gathered: step of the batch << 24 | neuron
-        uint64_t list1[kList1];            // one tile: step << 48 | row length << 32 | row start
-    };
-    uint64_t wst[kRW][kWave];              // per wave: run r's (start - records before it) | step << 48
+    uint64_t list1[MULTI ? 1 : kList1];    // one tile: the batch's spikes, step << 48 | row length << 32 | row start
+    uint64_t wst[kRW][MULTI ? kMany * kWave : kWave];  // per wave: run r's (start - records before it) | step << 48
     uint32_t hm[kRW][2 * kWin];            // per wave: bit f set: a run starts at record f of the windows
-    uint32_t cnt[kRingMaxT], pre[kRingMaxT];
-    uint32_t inl[kRingMaxT][kInline];
-    uint32_t ptot[4], pq[2][4], pstop[4];
+    uint32_t tw[kRW][16], ti[kRW][64], tm[kRW][2 * kMany];  // per wave: its tiles' spikes as one sequence
+    uint32_t cnt[kRingMaxT];               // raster: every tile's spikes in the batch
+    uint32_t stop;                         // a wave gave up waiting
     uint32_t own[kInline + 1];             // the tile's first spikes (the last entry: a dummy)
     uint32_t ntot[2];                      // spikes of the batch, by batch parity
     uint32_t nb[kRunMaxD];                 // ... of each step
@@ -192,8 +213,8 @@ __device__ __forceinline__ bool ring_neuron(const ModelArgs &m, float &V, uint32
 
 // Add the records of N windows (64 records each, from record f0 of the
 // wave's runs on) to the ring: every load is issued before the first add.
-template <bool FIXED, bool CMP, bool CNT, int N>
-__device__ __forceinline__ void ring_windows(const StepArgs &a, RingLDS<FIXED, CNT> &L, uint32_t w, uint32_t lane,
+template <bool FIXED, bool CMP, bool CNT, int N, class L_>
+__device__ __forceinline__ void ring_windows(const StepArgs &a, L_ &L, uint32_t w, uint32_t lane,
                                              uint32_t mw, uint32_t f0, uint32_t tot, uint32_t &base, uint32_t slot0)
 {
     using Rec = typename SynRec<CMP>::T;
@@ -227,46 +248,35 @@ __device__ __forceinline__ void ring_windows(const StepArgs &a, RingLDS<FIXED, C
     }
 }
 
-// Where a spike's run in this tile starts, and how long it is: loads issued
-// here, used later (the next group's are in flight while a group is walked).
-struct RunAt {
-    uint64_t row;    // the row's first synapse
-    uint32_t ends;   // the run's two ends in the row
-    uint32_t u;
-};
-__device__ __forceinline__ RunAt run_at(const StepArgs &a, uint32_t tile, uint32_t spike)
+// Walk a wave's runs (R per lane, len records from synapse beg on each) and
+// add their records to the ring.
+template <bool FIXED, bool CMP, bool CNT, int R, class L_>
+__device__ __forceinline__ void ring_walk(const StepArgs &a, L_ &L, uint32_t w, uint32_t lane, const uint64_t *beg,
+                                          const uint32_t *len, const uint32_t *u, uint32_t slot0)
 {
-    const uint32_t s = spike & kTargetMask;
-    RunAt r;
-    // (the two ends are neighbouring u16: one 4-byte load at 2-byte alignment)
-    __builtin_memcpy(&r.ends, a.toff + (uint64_t)s * (a.tl.T + 1) + tile, 4);
-    // rows of equal length start at a multiple of it; no load then
-    r.row = a.row_ptr[a.row_len ? 0u : s];
-    if (a.row_len) r.row = (uint64_t)s * a.row_len;
-    r.u = spike >> kTargetBits;
-    return r;
-}
-
-// Walk a wave's runs (one per lane, len records from synapse beg on) and add
-// their records to the ring.
-template <bool FIXED, bool CMP, bool CNT>
-__device__ __forceinline__ void ring_walk(const StepArgs &a, RingLDS<FIXED, CNT> &L, uint32_t w, uint32_t lane,
-                                          uint64_t beg, uint32_t len, uint32_t u, uint32_t slot0)
-{
-    const uint32_t inc = wave_scan_incl_u32(len), pre = inc - len;
-    const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
-    const uint64_t some = __ballot(len != 0);
-    if (len) {
-        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32),
-                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0u));
-        L.wst[w][rank] = ((beg - pre) & kBegMask) | (uint64_t)u << 48;
+    uint32_t pre[R], tot = 0, runs = 0;
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const uint32_t inc = wave_scan_incl_u32(len[r]);
+        pre[r] = tot + inc - len[r];
+        tot += (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+        const uint64_t some = __ballot(len[r] != 0);
+        if (len[r]) {
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)some, runs));
+            L.wst[w][rank] = ((beg[r] - pre[r]) & kBegMask) | (uint64_t)u[r] << 48;
+        }
+        runs += (uint32_t)__popcll(some);
     }
     uint32_t base = 0;  // runs that start before the windows
     for (uint32_t f0 = 0; f0 < tot; f0 += kWin * kWave) {
         if (lane < 2 * kWin) L.hm[w][lane] = 0;
         lds_wave_sync();
-        const uint32_t o = pre - f0;
-        if (len && o < kWin * kWave) atomicOr(&L.hm[w][o >> 5], 1u << (o & 31u));
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const uint32_t o = pre[r] - f0;
+            if (len[r] && o < kWin * kWave) atomicOr(&L.hm[w][o >> 5], 1u << (o & 31u));
+        }
         lds_wave_sync();
         const uint32_t mw = L.hm[w][lane & (2 * kWin - 1)];
         const uint32_t nwin = (tot - f0 + kWave - 1) / kWave;
@@ -284,58 +294,165 @@ __device__ __forceinline__ void ring_walk(const StepArgs &a, RingLDS<FIXED, CNT>
     }
 }
 
-// Deliver the K spikes of the list into the ring: each wave takes groups of
-// at most 64.
-template <bool FIXED, bool CMP, bool CNT, bool MULTI>
-__device__ __forceinline__ void ring_gather(const StepArgs &a, RingLDS<FIXED, CNT> &L, uint32_t tile, uint32_t K,
-                                            uint32_t slot0)
+// One tile: deliver the K spikes of the list into the ring; each wave takes
+// groups of at most 64.
+template <bool FIXED, bool CMP, bool CNT, class L_>
+__device__ __forceinline__ void ring_gather1(const StepArgs &a, L_ &L, uint32_t K, uint32_t slot0)
 {
     const uint32_t lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     uint32_t G = (K + kRW - 1) / kRW;  // spikes per wave and round
     G = G > (uint32_t)kWave ? (uint32_t)kWave : G;
-    uint32_t p0 = w * G;
-    if (p0 >= K) return;
-    if constexpr (!MULTI) {
-        for (; p0 < K; p0 += kRW * G) {
-            const bool live = lane < G && p0 + lane < K;
-            const uint64_t en = L.list1[live ? p0 + lane : p0];
-            ring_walk<FIXED, CMP, CNT>(a, L, w, lane, (uint32_t)en, live ? (uint32_t)(en >> 32) & 0xffffu : 0u,
-                                       (uint32_t)(en >> 48), slot0);
-        }
-    } else {
-        RunAt nx = run_at(a, tile, L.list[lane < G && p0 + lane < K ? p0 + lane : p0]);
-        for (; p0 < K; p0 += kRW * G) {
-            const RunAt r = nx;
-            const bool live = lane < G && p0 + lane < K;
-            const uint32_t n0 = p0 + kRW * G;
-            nx = run_at(a, tile, L.list[lane < G && n0 + lane < K ? n0 + lane : p0]);
-            const uint32_t b = r.ends & 0xffffu;
-            ring_walk<FIXED, CMP, CNT>(a, L, w, lane, r.row + b, live ? (r.ends >> 16) - b : 0u, r.u, slot0);
-        }
+    for (uint32_t p0 = w * G; p0 < K; p0 += kRW * G) {
+        const bool live = lane < G && p0 + lane < K;
+        const uint64_t en = L.list1[live ? p0 + lane : p0];
+        const uint64_t beg = (uint32_t)en;
+        const uint32_t len = live ? (uint32_t)(en >> 32) & 0xffffu : 0u, u = (uint32_t)(en >> 48);
+        ring_walk<FIXED, CMP, CNT, 1>(a, L, w, lane, &beg, &len, &u, slot0);
     }
 }
 
-// What a polling lane has seen of its tile's mailbox.
-struct Seen {
-    uint64_t a, b;
+// Several tiles: the lane's part of the spikes.  The wave's tiles are w,
+// w + 16, ... (lane / LP of them), or, with fewer than 16 tiles, tile w % Tn
+// shared by the waves w, w + Tn, ...
+struct Share {
+    uint32_t tile;   // the lane's tile
+    uint32_t i0;     // its first spike of the tile, and the distance to the next
+    uint32_t step;
+    uint32_t part, parts;  // the wave's part of its tile's spikes
+    bool mine;
 };
-
-// A wave's mailboxes are complete: their counts, the exclusive prefix of the
-// counts within the wave, their sum and the carried spikes go to LDS.
-template <class L_>
-__device__ __forceinline__ void ring_take(L_ &L, uint32_t w, uint32_t lane, bool mine, const Seen &v)
+__device__ __forceinline__ Share ring_share(uint32_t Tn, uint32_t w, uint32_t lane)
 {
-    uint32_t c = mine ? box_cnt(v.a) : 0u;
-    c = c < kMaxTileW ? c : kMaxTileW;
-    const uint32_t inc = wave_scan_incl_u32(c), tile = w * kWave + lane;
-    if (mine) {
-        L.cnt[tile] = c;
-        L.pre[tile] = inc - c;
-        L.inl[tile][0] = (uint32_t)(v.a >> 36);
-        L.inl[tile][1] = (uint32_t)((v.b >> 8) & kIdMask);
-        L.inl[tile][2] = (uint32_t)(v.b >> 36);
+    Share h;
+    if (Tn >= kRW) {
+        uint32_t lp = kWave;  // lanes per tile (uniform)
+        while ((kWave / lp) * kRW < Tn) lp >>= 1;
+        const uint32_t l = lane / lp;
+        h.tile = w + kRW * l;
+        h.mine = h.tile < Tn;
+        h.i0 = lane & (lp - 1u);
+        h.step = lp;
+        h.part = 0;
+        h.parts = 1;
+    } else {
+        const uint32_t q = kRW / Tn, part = w / Tn;  // waves per tile
+        h.tile = w - part * Tn;
+        h.mine = part < q;
+        h.i0 = part * kWave + lane;
+        h.step = q * kWave;
+        h.part = part;
+        h.parts = q;
     }
-    if (lane == kWave - 1) L.ptot[w] = inc;
+    if (!h.mine) h.tile = 0;
+    return h;
+}
+
+// Deliver the wave's spikes (the mailboxes of the lanes' tiles have arrived)
+// into the ring.  Few spikes: one or two per lane, as the lanes hold them.
+// More: the tiles' spikes as one sequence in tile order, up to kMany * 64 at a
+// time: neighbouring lanes then read rows and row offsets of one tile's
+// neurons, whose pages are few (lanes spread over all of the wave's tiles
+// instead took 75 us per step on 1e6 sources at 10 Hz, 41 spikes per tile;
+// the sequence takes 50; one tile after the other from a list of all
+// spikes, 64 at a time, 60).  Where each tile has a lane per spike, the
+// sequence's extra LDS round trips cost more than they save (120,000
+// neurons, 1 spike per tile: 6.3 against 5.5 us).
+template <bool FIXED, bool CMP, bool CNT, class L_>
+__device__ __forceinline__ void ring_gather(const StepArgs &a, L_ &L, uint32_t tile, uint32_t w, uint32_t lane,
+                                            const Share &h, Box box, const uint32_t *seg0, uint32_t seg_cap,
+                                            uint32_t slot0)
+{
+    const uint32_t c = h.mine ? box_cnt(box) : 0u, i = h.i0;
+    if (!__ballot(c != 0)) return;
+    const uint32_t row_len = a.row_len;
+    // where spike id's run starts (*beg: its row) and ends in the row
+    auto resolve = [&](bool in, uint32_t id, uint64_t *beg, uint32_t *ends) {
+        const uint32_t s = in ? id & kTargetMask : 0u;
+        // (the run's two ends are neighbouring u16: one 4-byte load at 2-byte alignment)
+        __builtin_memcpy(ends, a.toff + (uint64_t)s * (a.tl.T + 1) + tile, 4);
+        // rows of equal length start at a multiple of it; no load then
+        *beg = row_len ? (uint64_t)s * row_len : a.row_ptr[s];
+    };
+    if (!__ballot(i + h.step < c)) {
+        const bool in = i < c;
+        if (!__ballot(in)) return;  // (several waves share the tile)
+        uint32_t id = box_spike(box, i);
+        if (c > kInline) id = ld_ag(seg0 + (uint64_t)h.tile * seg_cap + (in ? i : 0u));
+        const uint32_t u = id >> kTargetBits;
+        uint64_t beg;
+        uint32_t ends;
+        resolve(in, id, &beg, &ends);
+        beg += ends & 0xffffu;
+        const uint32_t len = in ? (ends >> 16) - (ends & 0xffffu) : 0u;
+        ring_walk<FIXED, CMP, CNT, 1>(a, L, w, lane, &beg, &len, &u, slot0);
+        return;
+    }
+    uint32_t id[kMany], at[kMany], base = 0;
+    // the first lane of each tile: its spikes are positions pre .. pre + n - 1
+    const bool first = h.mine && (h.i0 & (kWave - 1u)) == 0;
+    const uint32_t n0 = h.parts > 1 ? c * h.part / h.parts : 0u, n1 = h.parts > 1 ? c * (h.part + 1) / h.parts : c;
+    const uint32_t n = first ? n1 - n0 : 0u;
+    const uint32_t inc = wave_scan_incl_u32(n), pre = inc - n;
+    const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+    const uint64_t some = __ballot(n != 0);
+    if (n) {
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0u));
+        // position p of rank r's spikes: word tw[r] + p of the segments, or of
+        // the carried spikes in ti (bit 31)
+        L.tw[w][rank] = c > kInline ? h.tile * seg_cap + n0 - pre : 0x80000000u | ((rank * 4 + n0 - pre) & 0x7fffffffu);
+#pragma unroll
+        for (uint32_t k = 0; k < kInline; k++) L.ti[w][rank * 4 + k] = box_spike(box, k);
+    }
+    lds_wave_sync();
+    // the places of the R * 64 spikes of the sequence from p0 on (base: tiles
+    // that start before p0)
+    auto locate = [&](uint32_t p0) {
+        if (lane < 2 * kMany) L.tm[w][lane] = 0;
+        lds_wave_sync();
+        const uint32_t o = pre - p0;
+        if (n && o < kMany * kWave) atomicOr(&L.tm[w][o >> 5], 1u << (o & 31u));
+        lds_wave_sync();
+        const uint32_t mw = L.tm[w][lane & (2 * kMany - 1)];
+#pragma unroll
+        for (int r = 0; r < kMany; r++) {
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)mw, 2 * r),
+                           hi = (uint32_t)__builtin_amdgcn_readlane((int)mw, 2 * r + 1);
+            const uint64_t m = (uint64_t)hi << 32 | lo, m1 = m >> 1;
+            const uint32_t k = __builtin_amdgcn_mbcnt_hi((uint32_t)(m1 >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m1, base + (lo & 1u) - 1u));
+            base += (uint32_t)__popcll(m);
+            const uint32_t v = L.tw[w][k & 15u], p = p0 + r * kWave + lane;
+            at[r] = (v & 0x80000000u) | ((v + p) & 0x7fffffffu);
+            if (p < tot && !(at[r] >> 31)) id[r] = ld_ag(seg0 + at[r]);
+        }
+    };
+#pragma unroll
+    for (int r = 0; r < kMany; r++) id[r] = 0;
+    locate(0);
+    for (uint32_t p0 = 0; p0 < tot; p0 += kMany * kWave) {
+        uint64_t beg[kMany];
+        uint32_t len[kMany], u[kMany], ends[kMany];
+#pragma unroll
+        for (int r = 0; r < kMany; r++) {
+            const bool in = p0 + r * kWave + lane < tot;
+            if (in && (at[r] >> 31)) id[r] = L.ti[w][at[r] & 63u];  // (carried by the mailbox)
+            u[r] = id[r] >> kTargetBits;
+            resolve(in, id[r], &beg[r], &ends[r]);
+        }
+        if (p0 + kMany * kWave < tot) locate(p0 + kMany * kWave);  // (uniform) the next IDs, in flight during the walk
+#pragma unroll
+        for (int r = 0; r < kMany; r++) {
+            beg[r] += ends[r] & 0xffffu;
+            len[r] = p0 + r * kWave + lane < tot ? (ends[r] >> 16) - (ends[r] & 0xffffu) : 0u;
+        }
+        ring_walk<FIXED, CMP, CNT, kMany>(a, L, w, lane, beg, len, u, slot0);
+    }
+}
+
+// Mailbox of a tile: the tiles that one wave polls (every 16th) lie together.
+__device__ __forceinline__ uint32_t ring_box(uint32_t tile)
+{
+    return (tile % kRW) * (kRingMaxT / kRW) + tile / kRW;
 }
 
 // The kernel's arguments, read again in each phase (scalar loads) instead of
@@ -353,7 +470,7 @@ __device__ __forceinline__ const RingArgs &ring_kargs()
 template <bool FIXED, bool CMP, bool CNT, bool MULTI, int NR>
 __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
 {
-    using LT = RingLDS<FIXED, CNT>;
+    using LT = RingLDS<FIXED, CNT, MULTI>;
     using AccT = typename LT::AccT;
     __shared__ LT L;
     const uint32_t tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -368,7 +485,7 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
     const uint32_t pslots = ring_kargs().s.pslots;
 
     float V[NR];
-    uint32_t R[NR];
+    uint32_t Rp[(NR + 3) / 4];    // refractory counters, a byte per neuron
     uint32_t rowb[NR], rowl[NR];  // one tile: the neuron's row
     {
         const RingArgs &ra = ring_kargs();
@@ -377,7 +494,8 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
         for (int r = 0; r < NR; r++) {
             const uint32_t q = r * kRT + tid, qc = q < tile_n ? tile_lo + q : tile_lo;
             V[r] = a.V[qc];
-            R[r] = a.ref[qc];
+            if (r % 4 == 0) Rp[r / 4] = 0;
+            Rp[r / 4] |= (uint32_t)a.ref[qc] << (8 * (r % 4));
             if constexpr (!MULTI) {
                 rowb[r] = (uint32_t)a.row_ptr[qc];
                 rowl[r] = (uint32_t)a.row_ptr[qc + 1] - rowb[r];
@@ -409,81 +527,36 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
     }
     uint64_t rbase = ring_kargs().s.raster_cap ? ring_kargs().s.raster_offs[t] : 0;
     uint32_t ps = (uint32_t)(t % pslots);  // ring slot of the batch's first step
-    uint32_t e = ring_kargs().e0, look = 0;
+    uint32_t e = ring_kargs().e0;
     const uint32_t dm = ring_kargs().s.dmin % pslots;
 
-    // Gather the spikes of batch e (first step in slot p): M of them, their
-    // counts and carried spikes in LDS (MULTI), or in the list (one tile).
-    auto gather = [&](uint32_t M, uint32_t p) {
-        const RingArgs &ra = ring_kargs();
-        const uint32_t sl0 = p + dm, slot0 = sl0 < pslots ? sl0 : sl0 - pslots;
-        constexpr uint32_t kChunk = MULTI ? kList : kList1;
-        for (uint32_t c0 = 0; c0 < M; c0 += kChunk) {
-            const uint32_t K = M - c0 < kChunk ? M - c0 : kChunk;
-            if constexpr (MULTI) {  // four threads per tile copy its spikes into the list
-                const uint32_t ti = tid >> 2, sub = tid & 3u;
-                static_assert(kRingMaxT * 4 <= kRT, "four threads per tile");
-                if (ti < Tn) {
-                    const uint32_t c = L.cnt[ti];
-                    uint32_t off = L.pre[ti];
-                    for (uint32_t k = 0; k < ti / kWave; k++) off += L.ptot[k];
-                    if (c <= kInline) {
-                        if (sub < c && off + sub - c0 < K) L.list[off + sub - c0] = L.inl[ti][sub];
-                    } else if (off < c0 + K && off + c > c0) {
-                        const uint32_t *src = ra.seg + ((uint64_t)(e & 1u) * Tn + ti) * ra.seg_cap;
-                        const uint32_t i0 = off < c0 ? c0 - off : 0u, i1 = off + c > c0 + K ? c0 + K - off : c;
-                        for (uint32_t i = i0 + sub; i < i1; i += 16) {
-                            uint32_t id[4];
-#pragma unroll
-                            for (int k = 0; k < 4; k++) id[k] = ld_ag(src + (i + 4 * k < i1 ? i + 4 * k : i));
-#pragma unroll
-                            for (int k = 0; k < 4; k++)
-                                if (i + 4 * k < i1) L.list[off + i + 4 * k - c0] = id[k];
-                        }
-                    }
-                }
-                lds_sync();
-            } else if (c0) {  // (spikes past the list's room, from the segment)
-                const uint32_t *src = ra.seg + (uint64_t)(e & 1u) * ra.seg_cap + c0;
-                for (uint32_t i = tid; i < K; i += kRT) {
-                    const uint32_t sp = ld_ag(src + i), s = sp & kTargetMask;
-                    const uint64_t b = ra.s.row_ptr[s];
-                    L.list1[i] = (uint64_t)(sp >> kTargetBits) << 48 | (ra.s.row_ptr[s + 1] - b) << 32 | b;
-                }
-                lds_sync();
-            }
-            ring_gather<FIXED, CMP, CNT, MULTI>(ra.s, L, tile, K, slot0);
-            if (c0 + K < M) lds_sync();  // the list is rebuilt
-        }
-    };
+    const Share share = ring_share(Tn, w, lane);
+    // where the events of a batch whose first step is in slot p are filed from
+    auto file_slot = [&](uint32_t p) { return p + dm < pslots ? p + dm : p + dm - pslots; };
+    if (tid == 0) L.stop = 0;
+    lds_sync();
 
-    if constexpr (MULTI) {
-        if (const uint32_t Dp = ring_kargs().pending) {  // the last launch's last batch
-            if (w * kWave < Tn) {
-                const uint32_t pt = w * kWave + lane;
-                const uint64_t *box = ring_kargs().ctl->box[e & 1u] + (uint64_t)(pt < Tn ? pt : 0u) * kRingBoxStride;
-                Seen v;
-                v.a = ld_ag64(box);
-                v.b = ld_ag64(box + 1);
-                ring_take(L, w, lane, pt < Tn, v);
-            }
-            lds_sync();
-            uint32_t M = 0;
-            for (uint32_t k = 0; k * kWave < Tn; k++) M += L.ptot[k];
-            gather(M, ps >= Dp ? ps - Dp : ps + pslots - Dp);
-            lds_sync();
+    // the first round gathers the last launch's last batch, if that was left
+    // to this launch, and nothing else
+    uint32_t left = MULTI ? ring_kargs().pending : 0u;
+    for (uint64_t s = 0; s < n_steps || left;) {
+        const bool run = !MULTI || left == 0;
+        const uint32_t Db = run ? (uint32_t)(n_steps - s < D ? n_steps - s : D) : left;
+        if (run) {
+            s += Db;
+            e++;
+        } else {
+            ps = ps >= Db ? ps - Db : ps + pslots - Db;
+            t -= Db;
         }
-    }
-
-    for (uint64_t s = 0; s < n_steps;) {
-        const uint32_t Db = (uint32_t)(n_steps - s < D ? n_steps - s : D);
-        s += Db;
-        e++;
         uint32_t *ntot = &L.ntot[e & 1u];
-        const uint32_t lists = ring_kargs().s.lists;
+        const uint32_t lists = ring_kargs().s.lists, row_len = ring_kargs().s.row_len;
+        uint32_t od[NR];  // out-degrees of the thread's neurons that fired (one-step batches; loads in flight)
+#pragma unroll
+        for (int r = 0; r < NR; r++) od[r] = 0;
 
         // 1. update
-        {
+        if (run) {
             const RingArgs &ra = ring_kargs();
             const ModelArgs &m = ra.s.m;
             uint32_t *seg = ra.seg + ((uint64_t)(e & 1u) * Tn + tile) * ra.seg_cap;
@@ -524,7 +597,9 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
                     if (live) L.ring[at0 + qc] = 0;
                     if constexpr (CNT) dl += live ? (acc & 0xffffu) + (acc >> 16) : 0u;
                     const float I = ring_input<FIXED, CNT>(m, acc, drive ? kq : 0u, w0, w1, q0, q1);
-                    bal[r] = __ballot(ring_neuron(m, V[r], R[r], I, (fire >> r) & 1u) && live);
+                    uint32_t ref = (Rp[r / 4] >> (8 * (r % 4))) & 0xffu;
+                    bal[r] = __ballot(ring_neuron(m, V[r], ref, I, (fire >> r) & 1u) && live);
+                    Rp[r / 4] = (Rp[r / 4] & ~(0xffu << (8 * (r % 4)))) | ref << (8 * (r % 4));
                     mine += (uint32_t)__popcll(bal[r]);
                 }
                 if (mine) {  // (uniform) one position counter update per wave
@@ -537,6 +612,7 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
                             put(wb + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal[r] >> 32),
                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)bal[r], 0u)), 0u, r);
                             if constexpr (!MULTI) el += rowl[r];
+                            else if (!row_len) od[r] = ra.s.outdeg[tile_lo + r * kRT + tid];
                         }
                         wb += (uint32_t)__popcll(bal[r]);
                     }
@@ -555,13 +631,14 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
                     const bool live = q < tile_n;
                     const uint32_t qc = live ? q : 0u;
                     if (!__ballot(live)) continue;  // (a wave without neurons)
+                    uint32_t ref = (Rp[r / 4] >> (8 * (r % 4))) & 0xffu;
                     for (uint32_t u = 0; u < Db; u++) {
                         const uint32_t sl = ps + u < pslots ? ps + u : ps + u - pslots;
                         const AccT acc = L.ring[sl * W + qc];
                         const uint32_t kq = L.kp[u * W + qc];
                         if (live) L.ring[sl * W + qc] = 0;
                         const float I = ring_input<FIXED, CNT>(m, acc, drive ? kq : 0u, w0, w1, q0, q1);
-                        const bool f = ring_neuron(m, V[r], R[r], I, (fire >> (u * nr + r)) & 1u) && live;
+                        const bool f = ring_neuron(m, V[r], ref, I, (fire >> (u * nr + r)) & 1u) && live;
                         const uint64_t bal = __ballot(f);
                         if (bal) {  // (uniform)
                             uint32_t wb = 0;
@@ -581,25 +658,26 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
                             if (lane == kWave - 1 && sum) atomicAdd(&L.dlv[u], sum);
                         }
                     }
+                    Rp[r / 4] = (Rp[r / 4] & ~(0xffu << (8 * (r % 4)))) | ref << (8 * (r % 4));
                 }
             }
         }
-        // 2. publication (the waves that poll are not those that store)
-        if (MULTI || ring_kargs().s.raster_cap) __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        const uint32_t cnt = *ntot;
-        if (!MULTI && cnt > kList1) {  // (spikes in the segment: stored before they are read)
+        // 2. publication
+        lds_sync();
+        const uint32_t cnt = run ? *ntot : 0u;
+        if (MULTI ? cnt > kInline : cnt > kList1 || ring_kargs().s.raster_cap) {
+            // (spikes in the segment: stored before they are announced or read)
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
         }
-        if (MULTI && w == kRW - 1) {
+        if (MULTI && run && w == kRW - 1) {
             const RingArgs &ra = ring_kargs();
             if (ra.s.raster_cap && Db > 1) {  // each step's count, for the raster positions
                 if (lane < Db) st_ag(&ra.cnts[((uint64_t)(e & 1u) * kRunMaxD + lane) * Tn + tile], L.nb[lane]);
                 __builtin_amdgcn_s_waitcnt(0);
             }
             if (lane == 0) {
-                uint64_t *box = ra.ctl->box[e & 1u] + (uint64_t)tile * kRingBoxStride;
+                uint64_t *box = ra.ctl->box[e & 1u] + (uint64_t)ring_box(tile) * kRingBoxStride;
                 st_ag64(box, box_a(e, cnt, L.own[0]));
                 st_ag64(box + 1, box_b(e, L.own[1], L.own[2]));
             }
@@ -610,104 +688,126 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
             const RingArgs &ra = ring_kargs();
             return ld_ag(ra.seg + ((uint64_t)(e & 1u) * Tn + tile) * ra.seg_cap + i);
         };
-        if (MULTI && !ring_kargs().s.row_len) {  // events emitted: the out-degrees of the tile's spikes
-            for (uint32_t i = tid; i < cnt; i += kRT) {
-                const uint32_t sp = own_spike(i);
-                atomicAdd(&L.ev[sp >> kTargetBits], (unsigned long long)ring_kargs().s.outdeg[sp & kTargetMask]);
-            }
-            __syncthreads();
-        }
-        if (w == kRW - 2 && lane < Db) {  // the steps' records
+        // the steps' records: spikes, events emitted, events delivered
+        if (run && w == kRW - 2 && lane < Db) {
             const StepArgs &a = ring_kargs().s;
             const uint64_t g = (t + lane) * kGroups + x;
             const uint32_t ns = Db == 1 ? cnt : L.nb[lane];
-            const unsigned long long ev = MULTI && a.row_len ? (unsigned long long)ns * a.row_len : L.ev[lane];
+            const unsigned long long ev = MULTI ? (unsigned long long)ns * row_len : L.ev[lane];
             if (ns) atomicAdd(&a.counts8[g], ns);
             if (ev) atomicAdd((unsigned long long *)&a.events8[g], ev);
-            if (CNT && lists > 1 && L.dlv[lane]) atomicAdd((unsigned long long *)&a.delivered8[g], (unsigned long long)L.dlv[lane]);
+            if (CNT && lists > 1 && L.dlv[lane])
+                atomicAdd((unsigned long long *)&a.delivered8[g], (unsigned long long)L.dlv[lane]);
             L.dlv[lane] = 0;
             L.ev[lane] = 0;
+            if (!a.raster_cap) L.nb[lane] = 0;
         }
-        if (MULTI && s >= n_steps && ring_kargs().defer) {  // the next launch gathers this batch
-            t += Db;
+        // rows of unequal length: the out-degrees of the tile's spikes, after
+        // the gather (their loads are in flight meanwhile)
+        auto emitted = [&] {
+            if (!MULTI || !run || row_len) return;
+            const StepArgs &a = ring_kargs().s;
+            if (Db == 1) {
+                uint32_t sum = 0;
+#pragma unroll
+                for (int r = 0; r < NR; r++) sum += od[r];
+                if (__ballot(sum != 0)) {
+                    const uint64_t ev = wave_sum_u64(sum);
+                    if (lane == 0) atomicAdd((unsigned long long *)&a.events8[t * kGroups + x], (unsigned long long)ev);
+                }
+            } else if (w == kRW - 2) {
+                for (uint32_t i = lane; i < cnt; i += kWave) {
+                    const uint32_t sp = own_spike(i);
+                    atomicAdd((unsigned long long *)&a.events8[(t + (sp >> kTargetBits)) * kGroups + x],
+                              (unsigned long long)a.outdeg[sp & kTargetMask]);
+                }
+            }
+        };
+        if (MULTI && run && s >= n_steps && ring_kargs().defer) {  // the next launch gathers this batch
+            emitted();
             break;
         }
 
-        // 3. the other tiles, and the next batch's draws
-        const uint32_t Dn = (uint32_t)(n_steps - s < D ? n_steps - s : D), units = Dn * nr;
-        uint32_t dk = 0, M = cnt, fire_n = 0;
-        if constexpr (MULTI) {
+        // 3. the other tiles, the next batch's draws, 4. the gather
+        const uint32_t Dn = (uint32_t)(n_steps - s < D ? n_steps - s : D), units = run ? Dn * nr : 0u;
+        uint32_t dk = 0, fire_n = 0;
+        {
             const RingArgs &ra = ring_kargs();
             const ModelArgs &m = ra.s.m;
-            const bool poller = w * kWave < Tn;
-            const uint32_t ptile = w * kWave + lane;
-            const bool mine = poller && ptile < Tn;
-            const uint64_t *box = ra.ctl->box[e & 1u] + (uint64_t)(mine ? ptile : 0u) * kRingBoxStride;
-            Seen v{(uint64_t)((e ^ 1u) & 0x3ffffu), 0};  // (not this batch's)
-            bool ready = false;
-            while (!ready && dk < units) {
-                if (mine && !box_ready(v.a, v.b, e)) {
-                    v.a = ld_ag64(box);
-                    v.b = ld_ag64(box + 1);
-                }
-                ring_draw(m, L, W, tile_lo, tile_n, t + Db, dk++, nr, &fire_n);
-                if (poller) {
-                    const bool ok = __all(!mine || box_ready(v.a, v.b, e));
-                    if (ok) ring_take(L, w, lane, mine, v);
-                    if (lane == 0) L.pq[look & 1u][w] = ok ? 1u : 0u;
-                }
-                __syncthreads();
-                ready = true;
-                for (uint32_t k = 0; k * kWave < Tn; k++) ready = ready && L.pq[look & 1u][k] != 0;
-                look++;  // (pq of this parity is written again two looks later, after a barrier)
-            }
-            if (!ready) {
-                if (poller) {
-                    const uint64_t c0 = wall_clock64();
-                    bool ok = true;
-                    for (uint32_t k = 0;; k++) {
-                        if (mine && !box_ready(v.a, v.b, e)) {
-                            v.a = ld_ag64(box);
-                            v.b = ld_ag64(box + 1);
+            if constexpr (MULTI) {
+                const uint64_t *box = ra.ctl->box[e & 1u];
+                const uint32_t bk = ring_box(share.tile);
+                Box v{(e ^ 1u) & 0x3ffffu, 0};  // (not this batch's)
+                bool ok = true;
+                uint64_t c0 = 0;
+                for (uint32_t k = 0;; k++) {
+                    if (share.mine && !box_ready(v, e)) v = box_load(box, bk);
+                    const bool draw = dk < units;
+                    if (draw) ring_draw(m, L, W, tile_lo, tile_n, t + Db, dk++, nr, &fire_n);
+                    if (__all(!share.mine || box_ready(v, e))) break;
+                    if (draw) continue;
+                    if (!c0) c0 = wall_clock64();
+                    if ((k & 31u) == 31u) {
+                        if (ld_ag(&ra.ctl->abort_flag)) {
+                            ok = false;
+                            break;
                         }
-                        if (__all(!mine || box_ready(v.a, v.b, e))) break;
-                        if ((k & 31u) == 31u) {
-                            if (ld_ag(&ra.ctl->abort_flag)) {
-                                ok = false;
-                                break;
-                            }
-                            if (wall_clock64() - c0 > kTicks) {
-                                if (lane == 0) atomicOr(&ra.ctl->abort_flag, kRunAbortTimeout);
-                                ok = false;
-                                break;
-                            }
+                        if (wall_clock64() - c0 > kTicks) {
+                            if (lane == 0) atomicOr(&ra.ctl->abort_flag, kRunAbortTimeout);
+                            ok = false;
+                            break;
                         }
-                        __builtin_amdgcn_s_sleep(1);
                     }
-                    if (ok) ring_take(L, w, lane, mine, v);
-                    if (lane == 0) {
-                        L.pstop[w] = ok ? 0u : 1u;
-                        if (!ok) atomicOr(ra.s.flags, kStopped);
-                    }
+                    __builtin_amdgcn_s_sleep(1);
                 }
-                __syncthreads();
-                uint32_t stop = 0;
-                for (uint32_t k = 0; k * kWave < Tn; k++) stop |= L.pstop[k];
-                if (stop) return;
+                if (ok) {
+                    if (ra.s.raster_cap && share.mine && share.i0 == 0) L.cnt[share.tile] = box_cnt(v);
+                    ring_gather<FIXED, CMP, CNT>(ra.s, L, tile, w, lane, share, v,
+                                                 ra.seg + (uint64_t)(e & 1u) * Tn * ra.seg_cap, ra.seg_cap,
+                                                 file_slot(ps));
+                } else if (lane == 0) {
+                    L.stop = 1;
+                    atomicOr(ra.s.flags, kStopped);
+                }
+            } else {
+                for (uint32_t c0 = 0; c0 < cnt; c0 += kList1) {
+                    const uint32_t K = cnt - c0 < kList1 ? cnt - c0 : kList1;
+                    if (c0) {  // (spikes past the list's room, from the segment)
+                        lds_sync();
+                        const uint32_t *src = ra.seg + (uint64_t)(e & 1u) * ra.seg_cap + c0;
+                        for (uint32_t i = tid; i < K; i += kRT) {
+                            const uint32_t sp = ld_ag(src + i), sn = sp & kTargetMask;
+                            const uint64_t b = ra.s.row_ptr[sn];
+                            L.list1[i] = (uint64_t)(sp >> kTargetBits) << 48 | (ra.s.row_ptr[sn + 1] - b) << 32 | b;
+                        }
+                        lds_sync();
+                    }
+                    ring_gather1<FIXED, CMP, CNT>(ra.s, L, K, file_slot(ps));
+                }
             }
-            M = 0;
-            for (uint32_t k = 0; k * kWave < Tn; k++) M += L.ptot[k];
+            emitted();
+            for (; dk < units; dk++) ring_draw(m, L, W, tile_lo, tile_n, t + Db, dk, nr, &fire_n);
         }
+        if (run) fire = fire_n;
         if (tid == 0) L.ntot[(e + 1u) & 1u] = 0;  // (last used before the previous batch's barriers)
+        lds_sync();  // every event of the batch is in the ring
+        if (MULTI && L.stop) return;
+        left = 0;
 
         // raster: every tile appends its own spikes
-        if (ring_kargs().s.raster_cap) {
+        if (run && ring_kargs().s.raster_cap) {
             const RingArgs &ra = ring_kargs();
             const StepArgs &a = ra.s;
-            uint32_t before = 0;
-            if (MULTI) {
-                before = L.pre[tile];
-                for (uint32_t k = 0; k < tile / kWave; k++) before += L.ptot[k];
+            uint32_t before = 0, M = cnt;
+            if (MULTI) {  // (each wave for itself)
+                uint32_t tot = 0, bef = 0;
+                for (uint32_t k = lane; k < Tn; k += kWave) {
+                    const uint32_t c = L.cnt[k];
+                    tot += c;
+                    bef += k < tile ? c : 0u;
+                }
+                M = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_incl_u32(tot), kWave - 1);
+                before = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_incl_u32(bef), kWave - 1);
             }
             if (Db == 1) {
                 const bool fits = rbase + M <= a.raster_cap;
@@ -759,18 +859,13 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
                 }
             }
         }
-        if (Db > 1 && w == kRW - 2 && lane < Db) L.nb[lane] = 0;  // (read by this wave, and above before a barrier)
-
-        // 4. gather, and the draws that are left
-        gather(M, ps);
-        {
-            const ModelArgs &m = ring_kargs().s.m;
-            for (; dk < units; dk++) ring_draw(m, L, W, tile_lo, tile_n, t + Db, dk, nr, &fire_n);
+        if (run && ring_kargs().s.raster_cap) {
+            __syncthreads();  // (own spikes and counts read before the next batch's)
+            if (tid < kRunMaxD) L.nb[tid] = 0;
+            __syncthreads();
         }
-        fire = fire_n;
         t += Db;
         ps = ps + Db < pslots ? ps + Db : ps + Db - pslots;
-        lds_sync();  // every event of the batch is in the ring
     }
 
     const RingArgs &ra = ring_kargs();
@@ -780,7 +875,7 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
         const uint32_t q = r * kRT + tid;
         if (q < tile_n) {
             a.V[tile_lo + q] = V[r];
-            if (a.m.kind != SPK_SOURCE) a.ref[tile_lo + q] = (uint8_t)R[r];
+            if (a.m.kind != SPK_SOURCE) a.ref[tile_lo + q] = (uint8_t)(Rp[r / 4] >> (8 * (r % 4)));
         }
     }
     AccT *ring_g = (AccT *)ra.ring + (uint64_t)tile * pslots * W;
@@ -831,7 +926,7 @@ bool ring_supported(const RingArgs &ra)
     if (ra.counts && !a.compact) return false;
     if (!ra.counts && a.lists > 1) return false;  // (deliveries per step are counted from the event counts)
     if (a.compact ? !a.syn32 : !a.syn) return false;
-    return (uint64_t)a.pslots * tl.W * ring_acc_bytes(a.m.fixed, ra.counts) <= kRingBytes;
+    return (uint64_t)a.pslots * tl.W * ring_acc_bytes(a.m.fixed, ra.counts) <= (ra.Tn == 1 ? kRingBytes1 : kRingBytes);
 }
 
 hipError_t launch_ring(const RingArgs &ra, hipStream_t s)

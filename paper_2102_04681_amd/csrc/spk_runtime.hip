@@ -592,7 +592,9 @@ void plan_ring(spk_net *net, uint64_t nnz_expected, const uint64_t *in_max)
     //   on 123; delay 15 and 1e9 synapses: 2.0 on 196, 2.6 on 98).
     const uint64_t nnz = nnz_expected;
     const bool fixed_cap = std::getenv("SPK_TILES_PER_XCD") != nullptr;
-    auto fits = [&](uint32_t W) { return (uint64_t)net->dmax * W * acc <= kRingBytes; };
+    auto fits = [&](uint32_t W) {
+        return (uint64_t)net->dmax * W * acc <= (W >= net->n ? kRingBytes1 : kRingBytes);
+    };
     auto tiles = [&](uint32_t W) { return (net->n + W - 1) / W; };
     uint32_t W = 0;
     if (fixed_cap) {
