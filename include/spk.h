@@ -47,7 +47,7 @@ extern "C" {
 
 #define SPK_ABI_VERSION 5u
 #define SPK_MAX_DELAY_LISTS 64u  /* delay_max - delay_min + 1 must not exceed this */
-/* Device scratch of spk_deliver_noalloc, per device (bytes). */
+/* Device scratch of spk_deliver_noalloc, per device (bytes; there are two such areas). */
 #define SPK_NOALLOC_SCRATCH_BYTES (32ull << 20)
 
 typedef enum {
@@ -290,11 +290,12 @@ spk_status spk_debug_deliver(spk_net *net, const uint32_t *spikes, uint64_t n_sp
  * and the output (d_out: n floats in fp32 mode, n int32 in fixed mode, units
  * of 2^-fixed_shift) in the caller's device memory, enqueued on the
  * network's stream and not waited for.  The pages, fill counters and
- * overflow accumulators the delivery needs come from one fixed scratch area
- * per device (SPK_NOALLOC_SCRATCH_BYTES, a static device array the library
- * holds until the process ends, cleared by a kernel at the start of every
- * call); the call allocates nothing, frees nothing, uses no memset and does
- * not synchronise.  Every call on one device shares that area: calls that
+ * overflow accumulators the delivery needs come from fixed scratch areas
+ * per device (SPK_NOALLOC_SCRATCH_BYTES each, static device arrays the
+ * library holds until the process ends; counters and accumulators are left at
+ * zero by every call); the call allocates nothing, frees nothing, uses no
+ * memset and does
+ * not synchronise.  Every call on one device shares them: calls that
  * overlap on one device (any network, any stream) race, so the caller
  * orders them (one stream, or events).  Networks with direct delivery need
  * no scratch.  Results equal spk_debug_deliver's.  Network state is not

@@ -360,6 +360,13 @@ hipError_t proc_in_abs_sum(const StepArgs &a, uint64_t *insum, hipStream_t s);
 hipError_t stream_copy(const void *src, void *dst, uint64_t bytes, hipStream_t s);
 hipError_t stream_read(const void *src, uint64_t bytes, uint32_t *sink, hipStream_t s);
 hipError_t zero_words(uint32_t *p, uint64_t n, hipStream_t s);
+// Readers: n steps' records summed over the groups (one of c32, c64), or the
+// state (V, then the refractory counters), with the flags, to host memory.
+constexpr uint32_t kStageWords = 16;             // words before the data
+constexpr uint64_t kStageBytes = 256ull << 10;   // of a network's pinned block
+hipError_t read_records(const uint32_t *c32, const uint64_t *c64, uint64_t t0, uint32_t n, const uint32_t *flags,
+                        uint32_t *dst, hipStream_t s);
+hipError_t read_state(const float *V, const uint8_t *ref, uint32_t n, const uint32_t *flags, uint32_t *dst, hipStream_t s);
 uint32_t push_blocks_per_group();
 
 // spk_run.hip -- the persistent step kernel (all steps of a call in one launch)

@@ -61,35 +61,93 @@ constexpr uint64_t kRunMaxSteps = 1ull << 24;      // steps per persistent launc
 constexpr uint64_t kRingPlainBatches = 3;          // batches of a call launched one by one (resident kernel)
 constexpr uint32_t kFlagRunStopped = 4u;           // device flag: a persistent launch stopped early
 
-// Scratch of spk_deliver_noalloc: one fixed area per device, held until the
+// Scratch of spk_deliver_noalloc: two fixed areas per device, held until the
 // process ends, shared by every call on that device (the caller orders
-// them).  In host code the array's name stands for a host-side shadow, not a
-// device address: kernels get the address hipGetSymbolAddress returned for
+// them).  `scratch` holds pages; `scratch_zero` the fill counters, overflow
+// flags and accumulators, which are zero between calls: the tile kernel puts
+// back to zero what the push kernel used, so that no call clears 4 or 8
+// bytes per neuron first (1e6 neurons, 1,000 spikes: 20.3 -> 17.2 us per call).
+// In host code the arrays' names stand for host-side shadows, not device
+// addresses: kernels get the addresses hipGetSymbolAddress returned for
 // the device, looked up once per device when a network is created there.
 constexpr uint64_t kNoAllocScratchBytes = SPK_NOALLOC_SCRATCH_BYTES;
 __device__ __align__(256) uint8_t scratch[kNoAllocScratchBytes];
+__device__ __align__(256) uint8_t scratch_zero[kNoAllocScratchBytes];
 constexpr int kMaxDevices = 64;
+struct Scratch {
+    uint8_t *pages = nullptr, *zero = nullptr;
+    bool unclean = false;  // a call's kernels were not all launched: the zero area is cleared by the next
+};
 std::mutex g_scratch_mu;
-void *g_scratch_ptr[kMaxDevices];
+Scratch g_scratch[kMaxDevices];
 
-// Address of this device's scratch (the device is current); looked up once.
+// Addresses of this device's scratch (the device is current); looked up once.
 spk_status scratch_lookup(int device)
 {
     if (device < 0 || device >= kMaxDevices) return fail(SPK_EINVAL, "device index beyond the scratch table");
     std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (g_scratch_ptr[device]) return SPK_OK;
-    void *p = nullptr;
+    if (g_scratch[device].pages) return SPK_OK;
+    void *p = nullptr, *z = nullptr;
     SPK_HIP(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-    if (!p) return fail(SPK_EHIP, "hipGetSymbolAddress returned no address for the scratch area");
-    g_scratch_ptr[device] = p;
+    SPK_HIP(hipGetSymbolAddress(&z, HIP_SYMBOL(scratch_zero)));
+    if (!p || !z) return fail(SPK_EHIP, "hipGetSymbolAddress returned no address for the scratch area");
+    g_scratch[device].zero = (uint8_t *)z;
+    g_scratch[device].pages = (uint8_t *)p;
     return SPK_OK;
 }
 
-void *scratch_of(int device)
+// Pinned host blocks for the readers, one per network while it lives; a few
+// are kept for the next networks (allocating one takes as long as creating a
+// small network).
+constexpr size_t kStageKeep = 4;
+std::mutex g_stage_mu;
+std::vector<uint32_t *> g_stage_free;
+
+uint32_t *stage_take()
 {
-    if (device < 0 || device >= kMaxDevices) return nullptr;
+    {
+        std::lock_guard<std::mutex> lock(g_stage_mu);
+        if (!g_stage_free.empty()) {
+            uint32_t *p = g_stage_free.back();
+            g_stage_free.pop_back();
+            return p;
+        }
+    }
+    void *p = nullptr;  // (mapped into every device's address space)
+    if (hipHostMalloc(&p, kStageBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return (uint32_t *)p;
+}
+
+void stage_give(uint32_t *p)
+{
+    if (!p) return;
+    {
+        std::lock_guard<std::mutex> lock(g_stage_mu);
+        if (g_stage_free.size() < kStageKeep) {
+            g_stage_free.push_back(p);
+            return;
+        }
+    }
+    (void)hipHostFree(p);
+}
+
+// The device's scratch, marked unclean until scratch_done.
+Scratch scratch_take(int device)
+{
+    if (device < 0 || device >= kMaxDevices) return Scratch{};
     std::lock_guard<std::mutex> lock(g_scratch_mu);
-    return g_scratch_ptr[device];
+    const Scratch x = g_scratch[device];
+    g_scratch[device].unclean = true;
+    return x;
+}
+
+void scratch_done(int device)
+{
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    g_scratch[device].unclean = false;
 }
 
 uint64_t prob_threshold(double p)
@@ -220,6 +278,7 @@ struct spk_net {
     uint32_t *raster = nullptr;
     uint64_t *raster_offs = nullptr;
     void *dbg_out = nullptr;
+    uint32_t *stage = nullptr;  // pinned host block of the readers (null: none could be had)
     uint64_t t = 0;
     uint64_t device_bytes = 0;
     std::vector<void *> allocs;
@@ -728,6 +787,7 @@ spk_status setup_stream(spk_net *net, void *stream)
         net->own_stream = true;
     }
     SPK_HIP(hipStreamCreateWithFlags(&net->cap_stream, hipStreamNonBlocking));
+    net->stage = stage_take();
     return SPK_OK;
 }
 
@@ -1083,11 +1143,9 @@ spk_status check_ready(spk_net *net)
     return SPK_OK;
 }
 
-spk_status sync_flags(spk_net *net, uint32_t *flags_out)
+// What the device flags say.
+spk_status check_flags(spk_net *net, uint32_t f, uint32_t *flags_out)
 {
-    SPK_HIP(hipStreamSynchronize(net->stream));
-    uint32_t f = 0;
-    SPK_HIP(hipMemcpy(&f, net->flags, 4, hipMemcpyDeviceToHost));
     if (flags_out) *flags_out = f;
     if (f & kFlagRunStopped)
         return fail(SPK_EHIP, "a persistent step launch stopped early (a barrier wait exceeded its "
@@ -1099,6 +1157,20 @@ spk_status sync_flags(spk_net *net, uint32_t *flags_out)
                                 "delivered nothing");
     }
     return SPK_OK;
+}
+
+spk_status sync_flags(spk_net *net, uint32_t *flags_out)
+{
+    uint32_t f = 0;
+    if (net->stage) {
+        SPK_HIP(read_records(nullptr, nullptr, 0, 0, net->flags, net->stage, net->stream));
+        SPK_HIP(hipStreamSynchronize(net->stream));
+        f = net->stage[0];
+    } else {
+        SPK_HIP(hipStreamSynchronize(net->stream));
+        SPK_HIP(hipMemcpy(&f, net->flags, 4, hipMemcpyDeviceToHost));
+    }
+    return check_flags(net, f, flags_out);
 }
 
 RunArgs run_args(const spk_net *net, uint64_t t0, uint64_t n_steps)
@@ -1329,12 +1401,22 @@ void destroy_net(spk_net *net)
     for (void *p : net->allocs) (void)hipFree(p);
     if (net->cap_stream) (void)hipStreamDestroy(net->cap_stream);
     if (net->own_stream && net->stream) (void)hipStreamDestroy(net->stream);
+    stage_give(net->stage);
     delete net;
 }
 
+// Records of n steps, summed over the groups, after the enqueued work.
 spk_status read_groups(spk_net *net, const void *dev, size_t elem, uint64_t t0, uint64_t n, void *out)
 {
-    (void)net;
+    if (net->stage && n * elem <= kStageBytes - kStageWords * 4) {
+        SPK_HIP(read_records(elem == 4 ? (const uint32_t *)dev : nullptr, elem == 8 ? (const uint64_t *)dev : nullptr, t0,
+                             (uint32_t)n, net->flags, net->stage, net->stream));
+        SPK_HIP(hipStreamSynchronize(net->stream));
+        SPK_TRY(check_flags(net, net->stage[0], nullptr));
+        if (n) std::memcpy(out, net->stage + kStageWords, n * elem);
+        return SPK_OK;
+    }
+    SPK_TRY(sync_flags(net, nullptr));
     std::vector<uint8_t> buf(n * kGroups * elem);
     if (n) SPK_HIP(hipMemcpy(buf.data(), (const uint8_t *)dev + t0 * kGroups * elem, buf.size(),
                              hipMemcpyDeviceToHost));
@@ -1644,7 +1726,6 @@ spk_status spk_read_spike_counts(spk_net *net, uint64_t t0, uint64_t n, uint32_t
 {
     SPK_TRY(check_ready(net));
     if (t0 + n > net->P.max_steps || (n && !out)) return fail(SPK_EINVAL, "range");
-    SPK_TRY(sync_flags(net, nullptr));
     return read_groups(net, net->counts8, 4, t0, n, out);
 }
 
@@ -1652,7 +1733,6 @@ spk_status spk_read_events(spk_net *net, uint64_t t0, uint64_t n, uint64_t *out)
 {
     SPK_TRY(check_ready(net));
     if (t0 + n > net->P.max_steps || (n && !out)) return fail(SPK_EINVAL, "range");
-    SPK_TRY(sync_flags(net, nullptr));
     return read_groups(net, net->events8, 8, t0, n, out);
 }
 
@@ -1660,14 +1740,13 @@ spk_status spk_read_delivered(spk_net *net, uint64_t t0, uint64_t n, uint64_t *o
 {
     SPK_TRY(check_ready(net));
     if (t0 + n > net->P.max_steps || (n && !out)) return fail(SPK_EINVAL, "range");
-    SPK_TRY(sync_flags(net, nullptr));
     if (net->ring && net->lists == 1) {
         // one delay: the events delivered at t are those emitted at t - dmin
         for (uint64_t k = 0; k < n && t0 + k < net->dmin; k++) out[k] = 0;
         const uint64_t skip = t0 < net->dmin ? std::min<uint64_t>(n, net->dmin - t0) : 0;
         const uint64_t last = std::max<uint64_t>(net->t, t0 + skip);  // steps not run yet deliver nothing
         const uint64_t m = std::min<uint64_t>(n - skip, last - (t0 + skip));
-        SPK_TRY(read_groups(net, net->events8, 8, t0 + skip - net->dmin, m, out + skip));
+        SPK_TRY(read_groups(net, net->events8, 8, m ? t0 + skip - net->dmin : 0, m, out + skip));
         for (uint64_t k = skip + m; k < n; k++) out[k] = 0;
         return SPK_OK;
     }
@@ -1696,6 +1775,14 @@ spk_status spk_read_raster(spk_net *net, uint64_t t0, uint64_t n, uint64_t *offs
 spk_status spk_read_state(spk_net *net, float *v, uint8_t *ref)
 {
     SPK_TRY(check_ready(net));
+    if (net->stage && (uint64_t)net->n * 5 + 8 <= kStageBytes - kStageWords * 4) {
+        SPK_HIP(read_state(net->V, net->ref, net->n, net->flags, net->stage, net->stream));
+        SPK_HIP(hipStreamSynchronize(net->stream));
+        SPK_TRY(check_flags(net, net->stage[0], nullptr));
+        if (v) std::memcpy(v, net->stage + kStageWords, (size_t)net->n * 4);
+        if (ref) std::memcpy(ref, net->stage + kStageWords + net->n, net->n);
+        return SPK_OK;
+    }
     SPK_TRY(sync_flags(net, nullptr));
     if (v) SPK_HIP(hipMemcpy(v, net->V, (size_t)net->n * 4, hipMemcpyDeviceToHost));
     if (ref) SPK_HIP(hipMemcpy(ref, net->ref, net->n, hipMemcpyDeviceToHost));
@@ -1777,8 +1864,6 @@ spk_status spk_deliver_noalloc(spk_net *net, const uint32_t *d_spikes, uint64_t 
     if (n_spikes > 0x3fffffffull || (n_spikes && !d_spikes)) return fail(SPK_EINVAL, "spikes");
     if (delay && (delay < net->dmin || delay >= net->dmin + net->lists))
         return fail(SPK_EINVAL, "delay not in [delay_min, delay_max]");
-    uint8_t *base = (uint8_t *)scratch_of(net->device);
-    if (!base) return fail(SPK_ESTATE, "no scratch address for the network's device");
     hipStream_t s = net->stream;
     const Tiling &tl = net->tl;
     StepArgs a = step_args(net);
@@ -1788,36 +1873,39 @@ spk_status spk_deliver_noalloc(spk_net *net, const uint32_t *d_spikes, uint64_t 
     a.dbg_out = d_out;  // (no spikes: the tile kernel writes zeros)
     hipError_t e = hipSuccess;
     if (!net->direct) {
-        // Carve the scratch: fill counters, overflow flags and overflow
-        // accumulators of one arrival slot, then pages of as many records as
-        // the rest holds (at most the debug capacity; events beyond it take
-        // the overflow accumulators, with the same sums)
+        // Carve the zero area: fill counters, overflow flags and overflow
+        // accumulators of one arrival slot; pages of as many records as the
+        // bytes they leave of one area's size hold (at most the debug
+        // capacity; events beyond it take the overflow accumulators, with the
+        // same sums)
         auto up = [](uint64_t b) { return (b + 255) / 256 * 256; };
         const uint64_t n_pages = (uint64_t)kGroups * net->pg1 * tl.T8;
         const uint64_t acc_bytes = (uint64_t)tl.T * tl.W * (net->P.acc_mode == SPK_ACC_FIXED ? 4 : 8);
         const uint64_t o_fill = 0, o_flag = up(n_pages * 4), o_acc = o_flag + up((uint64_t)tl.T * 4);
-        const uint64_t o_pages = o_acc + up(acc_bytes);
+        const uint64_t used = o_acc + up(acc_bytes);
         const uint64_t rec = net->compact ? 2 : 8;
-        const uint64_t room = o_pages < kNoAllocScratchBytes ? kNoAllocScratchBytes - o_pages : 0;
+        const uint64_t room = used < kNoAllocScratchBytes ? kNoAllocScratchBytes - used : 0;
         uint64_t cap = std::min<uint64_t>(room / (n_pages * rec), std::min<uint64_t>(kDebugPageCap, net->page_cap));
         cap = cap / 16 * 16;
         if (cap < 16)
             return fail(SPK_EOVERFLOW, "network too large for the fixed scratch of spk_deliver_noalloc (" +
                                            std::to_string(kNoAllocScratchBytes >> 20) + " MiB per device)");
-        a.pfill = (uint32_t *)(base + o_fill);
-        a.ovf_flag = (uint32_t *)(base + o_flag);
-        a.acc_ovf = base + o_acc;
-        a.pages = net->compact ? nullptr : (int2 *)(base + o_pages);
-        a.pages16 = net->compact ? (uint16_t *)(base + o_pages) : nullptr;
+        const Scratch x = scratch_take(net->device);
+        if (!x.pages) return fail(SPK_ESTATE, "no scratch address for the network's device");
+        a.pfill = (uint32_t *)(x.zero + o_fill);
+        a.ovf_flag = (uint32_t *)(x.zero + o_flag);
+        a.acc_ovf = x.zero + o_acc;
+        a.pages = net->compact ? nullptr : (int2 *)x.pages;
+        a.pages16 = net->compact ? (uint16_t *)x.pages : nullptr;
         a.page_cap = (uint32_t)cap;
         a.pslots = 1;
-        // counters, flags and accumulators start at zero (a fill kernel: the
-        // last call's contents stay in the scratch)
-        e = zero_words((uint32_t *)base, o_pages / 4, s);
+        // (a fill kernel, not a memset: usable under capture)
+        if (x.unclean) e = zero_words((uint32_t *)x.zero, kNoAllocScratchBytes / 4, s);
         if (e == hipSuccess && n_spikes) e = launch_push(a, 0, 0, s);
     }
     if (e == hipSuccess) e = launch_tile(a, 0, 0, s);
     if (e != hipSuccess) return fail(SPK_EHIP, hipGetErrorString(e));
+    if (!net->direct) scratch_done(net->device);
     return SPK_OK;
 }
 

@@ -308,7 +308,7 @@ __global__ __launch_bounds__(kTileThreads) void k_tile(StepArgs a, uint32_t i, i
 #pragma unroll
     for (int u = 0; u < kRounds; u++) {
         const uint32_t q = u * kTileThreads + tid;
-        const uint32_t gi = q < tile_n ? tile_lo + q : 0u;
+        const uint32_t gi = q < tile_n && !debug ? tile_lo + q : 0u;  // (debug: no update, one line for all)
         Vr[u] = a.V[gi];
         Rr[u] = a.ref[gi];
     }
@@ -563,6 +563,35 @@ __global__ __launch_bounds__(256) void k_zero_u32(uint32_t *p, uint64_t n)
     for (uint64_t k = (uint64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (uint64_t)gridDim.x * 256) p[k] = 0;
 }
 
+// Results of a reader call packed into its pinned host block: the network's
+// flags in word 0, the data from word kStageWords on.  One launch and one
+// wait instead of a wait and a copy for the flags and a copy per array.
+__global__ __launch_bounds__(256) void k_read_records(const uint32_t *c32, const uint64_t *c64, uint64_t t0, uint32_t n,
+                                                     const uint32_t *flags, uint32_t *dst)
+{
+    const uint32_t k = blockIdx.x * 256 + threadIdx.x;
+    if (k == 0) dst[0] = *flags;
+    if (k >= n) return;
+    uint64_t sum = 0;
+    for (uint32_t x = 0; x < kGroups; x++) sum += c32 ? c32[(t0 + k) * kGroups + x] : c64[(t0 + k) * kGroups + x];
+    if (c32) dst[kStageWords + k] = (uint32_t)sum;
+    else ((uint64_t *)(dst + kStageWords))[k] = sum;
+}
+
+__global__ __launch_bounds__(256) void k_read_state(const float *V, const uint8_t *ref, uint32_t n, const uint32_t *flags,
+                                                   uint32_t *dst)
+{
+    const uint32_t k = blockIdx.x * 256 + threadIdx.x;
+    if (k == 0) dst[0] = *flags;
+    if (k < n) dst[kStageWords + k] = __float_as_uint(V[k]);
+    const uint32_t b = 4 * k;  // (the counters of neurons b .. b + 3 in one word)
+    if (b < n) {
+        uint32_t w = 0;
+        for (uint32_t i = 0; i < 4; i++) w |= (b + i < n ? (uint32_t)ref[b + i] : 0u) << (8 * i);
+        dst[kStageWords + n + k] = w;
+    }
+}
+
 // Streaming read of n16 16-byte words, four loads in flight per thread; the
 // xor of everything read is stored only if it equals a value a memset never
 // produces, so the loads cannot be dropped and nothing is written.
@@ -642,6 +671,19 @@ hipError_t launch_record(const StepArgs &a, uint32_t i, int64_t t_explicit, hipS
 hipError_t launch_advance(uint64_t *t_base, uint32_t steps, hipStream_t s)
 {
     hipLaunchKernelGGL(k_advance, dim3(1), dim3(64), 0, s, t_base, steps);
+    return hipGetLastError();
+}
+
+hipError_t read_records(const uint32_t *c32, const uint64_t *c64, uint64_t t0, uint32_t n, const uint32_t *flags,
+                        uint32_t *dst, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_read_records, dim3(n / 256 + 1), dim3(256), 0, s, c32, c64, t0, n, flags, dst);
+    return hipGetLastError();
+}
+
+hipError_t read_state(const float *V, const uint8_t *ref, uint32_t n, const uint32_t *flags, uint32_t *dst, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_read_state, dim3(n / 256 + 1), dim3(256), 0, s, V, ref, n, flags, dst);
     return hipGetLastError();
 }
 
