@@ -137,10 +137,7 @@ enum { SPK_STEP_AUTO = 0, SPK_STEP_GRAPH = 1, SPK_STEP_PERSISTENT = 2 };
  *   SPK_BATCH_STEPS caps the
  *   steps per batch (1..16, default 8; spk_stats_t.batch_steps);
  *   SPK_RING=0 leaves out the steps with every pending input in LDS
- *   (spk_params.step_mode) and their tiling;
- *   SPK_GEN_KEYS=0 makes the Bernoulli generator draw every row a second
- *   time to place it instead of keeping the first pass's synapses (the
- *   results are the same). */
+ *   (spk_params.step_mode) and their tiling (the results are the same). */
 typedef struct {
     uint32_t abi_version;      /* must be SPK_ABI_VERSION */
     uint32_t n;

@@ -174,7 +174,7 @@ struct StepArgs {
     uint32_t proc;               // 1: procedural synapses (binned delivery; no rows stored)
     ProcArgs pr;
     int64_t wval[kMaxClasses];   // compact: weight of each class in accumulator units
-    const uint64_t *row_ptr;     // n + 1
+    const uint64_t *row_ptr;     // start of every row (lengths: outdeg)
     const int2 *syn;             // full: {j << 24 | target, weight bits (fp32 or quantised int32)}
     const uint32_t *syn32;       // compact: class << 30 | j << 24 | target
     const RowDesc *desc;         // binned: n
@@ -289,14 +289,16 @@ struct RingArgs {
 
 // spk_gen.hip -- connectivity expansion
 // hist: optional (Bernoulli rows), n * (T + 2 * kGroups) u16 bucket counts
-// kept for gen_fill_rows, which then need not count the rows again; keys
-// (with hist): n * cap u32, the first cap synapses of every row kept as
-// (delay index << 24 | target), so that gen_fill_rows need not draw the rows
-// again either (valid where no row is longer than cap).
-hipError_t gen_count_rows(const ConnArgs &c, uint32_t *cnt, uint16_t *hist, uint32_t *keys, uint32_t cap,
-                          hipStream_t s);
+// kept for gen_fill_rows, which then need not count the rows again.
+hipError_t gen_count_rows(const ConnArgs &c, uint32_t *cnt, uint16_t *hist, hipStream_t s);
 hipError_t gen_fill_rows(const ConnArgs &c, const uint64_t *row_ptr, void *syn, RowIndex ix,
-                         const uint16_t *hist, const uint32_t *keys, uint32_t cap, hipStream_t s);
+                         const uint16_t *hist, hipStream_t s);
+// Bernoulli rows grouped by tile, drawn once, for expected rows well below
+// kBernStage: syn has room synapses; *cursor (zero on entry) ends as their
+// number, or beyond room where the rows did not fit.
+constexpr uint32_t kBernStage = 8192;
+hipError_t gen_bern_once(const ConnArgs &c, uint64_t room, uint64_t *cursor, uint32_t *max_row, uint64_t *row_ptr,
+                         uint32_t *outdeg, uint16_t *toff, void *syn, hipStream_t s);
 hipError_t gen_in_count(const ConnArgs &c, uint32_t *cnt, hipStream_t s);
 hipError_t gen_in_fill(const ConnArgs &c, const uint64_t *row_ptr, uint32_t *cursor, void *syn,
                        hipStream_t s);
@@ -316,6 +318,9 @@ struct ClassTab {
 };
 hipError_t in_abs_sum(const void *syn, uint64_t nnz, bool fixed, bool compact, const ClassTab &tab,
                       uint64_t *insum, hipStream_t s);
+// The same sums from rows grouped by tile (toff); insum (n entries) zero on entry.
+hipError_t rows_abs_sum(const ConnArgs &c, const uint64_t *row_ptr, const void *syn, const uint16_t *toff,
+                        const ClassTab &tab, uint64_t *insum, hipStream_t s);
 hipError_t max_u64(const uint64_t *x, uint64_t m, uint64_t *out, hipStream_t s);
 // Fixed out-degree networks with population weights: the largest in_abs_sum
 // from the synapses drawn again and filed by target tile (no atomic per
@@ -336,7 +341,7 @@ uint32_t bern_src_ranges(uint32_t n);
 hipError_t bern_in_abs_max(const ConnArgs &c, uint64_t *out, uint64_t *insum, hipStream_t s);
 hipError_t init_state(const ModelArgs &m, float v0_lo, float v0_hi, float *V, uint8_t *ref,
                       hipStream_t s);
-hipError_t export_gather(const uint64_t *row_ptr, const void *syn, bool compact, const ClassTab &tab,
+hipError_t export_gather(const uint64_t *row_ptr, const uint32_t *outdeg, const void *syn, bool compact, const ClassTab &tab,
                          uint32_t dmin, const uint32_t *rows, uint64_t n_rows, const uint64_t *out_off,
                          uint32_t *col, uint32_t *wbits, uint8_t *delay, hipStream_t s);
 int cu_count();

@@ -498,7 +498,7 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
             Rp[r / 4] |= (uint32_t)a.ref[qc] << (8 * (r % 4));
             if constexpr (!MULTI) {
                 rowb[r] = (uint32_t)a.row_ptr[qc];
-                rowl[r] = (uint32_t)a.row_ptr[qc + 1] - rowb[r];
+                rowl[r] = a.outdeg[qc];
             }
         }
         const AccT *ring_g = (const AccT *)ra.ring + (uint64_t)tile * pslots * W;
@@ -778,7 +778,7 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
                         for (uint32_t i = tid; i < K; i += kRT) {
                             const uint32_t sp = ld_ag(src + i), sn = sp & kTargetMask;
                             const uint64_t b = ra.s.row_ptr[sn];
-                            L.list1[i] = (uint64_t)(sp >> kTargetBits) << 48 | (ra.s.row_ptr[sn + 1] - b) << 32 | b;
+                            L.list1[i] = (uint64_t)(sp >> kTargetBits) << 48 | (uint64_t)ra.s.outdeg[sn] << 32 | b;
                         }
                         lds_sync();
                     }

@@ -522,7 +522,7 @@ bool range_by_tiles(const spk_net *net)
 {
     if (net->P.conn_kind != SPK_CONN_FIXED_OUT || !net->compact || net->n_cls > 2) return false;
     if (const char *e = std::getenv("SPK_RANGE_PASS")) return std::strcmp(e, "atomics") != 0;
-    return true;
+    return !net->toff;  // (rows grouped by tile are summed as they are)
 }
 
 // Largest in_abs_sum of a fixed out-degree network by tiles (range_by_tiles);
@@ -861,8 +861,11 @@ spk_status choose_delivery(spk_net *net, RowIndex *ix)
 spk_status finish_rows(spk_net *net)
 {
     hipStream_t s = net->stream;
-    SPK_TRY(dalloc(net, &net->outdeg, net->n));
-    if (net->proc) {  // every row has k_out synapses
+    const bool have_deg = net->outdeg != nullptr;
+    if (!have_deg) SPK_TRY(dalloc(net, &net->outdeg, net->n));
+    if (have_deg) {
+        // (written with the rows)
+    } else if (net->proc) {  // every row has k_out synapses
         const std::vector<uint32_t> deg(net->n, net->P.k_out);
         SPK_HIP(hipMemcpyAsync(net->outdeg, deg.data(), (size_t)net->n * 4, hipMemcpyHostToDevice, s));
         SPK_HIP(hipStreamSynchronize(s));
@@ -888,6 +891,22 @@ spk_status finish_rows(spk_net *net)
         SPK_TRY(abs_term(net, net->P.w_exc, &te));
         SPK_TRY(abs_term(net, net->P.w_inh, &ti));
         m = (uint64_t)net->P.k_in_exc * te + (uint64_t)net->P.k_in_inh * ti;
+    } else if (net->toff && !std::getenv("SPK_RANGE_PASS")) {
+        // rows grouped by tile: summed tile by tile in LDS
+        uint64_t *insum = nullptr, *mx = nullptr;
+        SPK_TRY(dalloc(net, &insum, net->n));
+        SPK_TRY(dalloc(net, &mx, 1));
+        SPK_HIP(hipMemsetAsync(insum, 0, (size_t)net->n * 8, s));
+        SPK_HIP(hipMemsetAsync(mx, 0, 8, s));
+        SegTimer tm;
+        SPK_HIP(tm.start(s));
+        SPK_HIP(rows_abs_sum(conn_args(net), net->row_ptr, syn_ptr(net), net->toff, net->ctab, insum, s));
+        SPK_HIP(max_u64(insum, net->n, mx, s));
+        SPK_HIP(tm.stop(s, &net->range_ms));
+        SPK_HIP(hipMemcpyAsync(&m, mx, 8, hipMemcpyDeviceToHost, s));
+        SPK_HIP(hipStreamSynchronize(s));
+        dfree(net, insum);
+        dfree(net, mx);
     } else if (range_by_targets(net)) {
         // Bernoulli: the pair predicate evaluated per target (n^2 hashes)
         // costs less than a global atomic per synapse above ~1.4 % density
@@ -1021,9 +1040,64 @@ spk_status generate_proc(spk_net *net)
     return finish_rows(net);
 }
 
+// Bernoulli rows of a network of the resident kernel, drawn once: *ok =
+// false (and nothing left behind) where they do not suit or did not fit.
+spk_status generate_bern_once(spk_net *net, bool *ok)
+{
+    *ok = false;
+    const double p = net->P.p, nn = (double)net->n, sd = std::sqrt(nn * p * (1.0 - p));
+    // (the stage has a part for each of four waves, a quarter of the targets)
+    if (!net->ring || net->P.conn_kind != SPK_CONN_BERNOULLI || nn * p / 4 + 5.0 * sd + 64.0 > (double)kBernStage / 4)
+        return SPK_OK;
+    hipStream_t s = net->stream;
+    const uint64_t room = (uint64_t)(nn * nn * p + 10.0 * std::sqrt(nn) * sd) + 64;
+    void *syn = nullptr;
+    uint64_t *cursor = nullptr;
+    uint32_t *mx = nullptr;
+    SPK_TRY(dalloc(net, &net->row_ptr, (size_t)net->n + 1));
+    SPK_TRY(dalloc(net, &net->outdeg, net->n));
+    SPK_TRY(dalloc(net, &net->toff, (size_t)net->n * (net->tl.T + 1)));
+    SPK_TRY(alloc_syn(net, &syn, room));
+    SPK_TRY(dalloc(net, &cursor, 1));
+    SPK_TRY(dalloc(net, &mx, 1));
+    SPK_HIP(hipMemsetAsync(cursor, 0, 8, s));
+    SPK_HIP(hipMemsetAsync(mx, 0, 4, s));
+    SegTimer tm;
+    SPK_HIP(tm.start(s));
+    SPK_HIP(gen_bern_once(conn_args(net), room, cursor, mx, net->row_ptr, net->outdeg, net->toff, syn, s));
+    SPK_HIP(tm.stop(s, &net->gen_ms));
+    uint64_t nnz = 0;
+    uint32_t mr = 0;
+    SPK_HIP(hipMemcpyAsync(&nnz, cursor, 8, hipMemcpyDeviceToHost, s));
+    SPK_HIP(hipMemcpyAsync(&mr, mx, 4, hipMemcpyDeviceToHost, s));
+    SPK_HIP(hipStreamSynchronize(s));
+    dfree(net, cursor);
+    dfree(net, mx);
+    if (nnz > room) {
+        dfree(net, syn);
+        dfree(net, net->row_ptr);
+        dfree(net, net->outdeg);
+        dfree(net, net->toff);
+        net->row_ptr = nullptr;
+        net->outdeg = nullptr;
+        net->toff = nullptr;
+        return SPK_OK;
+    }
+    if (net->compact) net->syn32 = (uint32_t *)syn;
+    else net->syn = (int2 *)syn;
+    net->nnz = nnz;
+    net->max_row = mr;
+    net->direct = true;
+    *ok = true;
+    return SPK_OK;
+}
+
 spk_status generate(spk_net *net)
 {
     if (net->proc) return generate_proc(net);
+    bool once = false;
+    SPK_TRY(generate_bern_once(net, &once));
+    if (once) return finish_rows(net);
     hipStream_t s = net->stream;
     uint32_t *cnt = nullptr;
     SPK_TRY(dalloc(net, &cnt, net->n));
@@ -1042,33 +1116,12 @@ spk_status generate(spk_net *net)
         hist = nullptr;          // (then the placement pass counts for itself)
         (void)hipGetLastError();  // the failed allocation is not an error of the launches below
     }
-    // ... and keeps each row's synapses, up to cap = mean + 10 sd + 64 per
-    // row, so that the placement pass need not draw the rows again (unless a
-    // row turns out longer, or the keys would take more than 32 GB)
-    uint32_t *keys = nullptr;
-    uint32_t cap = 0;
-    const char *gk = std::getenv("SPK_GEN_KEYS");
-    if (hist && !(gk && std::strcmp(gk, "0") == 0)) {
-        const double p = net->P.p, nn = (double)net->n;
-        const double capd = std::ceil(p * nn + 10.0 * std::sqrt(nn * p * (1.0 - p)) + 64.0);
-        if (capd <= (double)kMaxRow && (double)net->n * capd * 4.0 <= (double)(32ull << 30)) {
-            cap = (uint32_t)capd;
-            if (dalloc(net, &keys, (size_t)net->n * cap) != SPK_OK) {
-                keys = nullptr;
-                (void)hipGetLastError();
-            }
-        }
-    }
     SegTimer tm;
     SPK_HIP(tm.start(s));
     if (in_rows) SPK_HIP(gen_in_count(c, cnt, s));
-    else SPK_HIP(gen_count_rows(c, cnt, hist, keys, cap, s));
+    else SPK_HIP(gen_count_rows(c, cnt, hist, s));
     SPK_HIP(tm.stop(s, &net->gen_ms));
     SPK_TRY(finish_counts(net, cnt));
-    if (keys && net->max_row > cap) {  // a row did not fit: placement draws the rows again
-        dfree(net, keys);
-        keys = nullptr;
-    }
     RowIndex ix{};
     SPK_TRY(choose_delivery(net, &ix));
     void *syn = nullptr;
@@ -1086,13 +1139,12 @@ spk_status generate(spk_net *net)
         dfree(net, tmp);
     } else {        // drawn per source, bucketed while drawn
         SPK_HIP(tm.start(s));
-        SPK_HIP(gen_fill_rows(c, net->row_ptr, syn, ix, hist, keys, cap, s));
+        SPK_HIP(gen_fill_rows(c, net->row_ptr, syn, ix, hist, s));
         SPK_HIP(tm.stop(s, &net->gen_ms));
     }
     SPK_HIP(hipStreamSynchronize(s));
     dfree(net, cnt);
     dfree(net, hist);
-    dfree(net, keys);
     return finish_rows(net);
 }
 
@@ -1941,7 +1993,7 @@ spk_status spk_export_rows(spk_net *net, const uint32_t *rows, uint64_t n_rows, 
     if (net->proc)
         SPK_HIP(export_proc(step_args(net), net->ctab, d_rows, n_rows, d_off, d_col, d_wb, d_del, s));
     else
-        SPK_HIP(export_gather(net->row_ptr, syn_ptr(net), net->compact, net->ctab, net->dmin, d_rows, n_rows,
+        SPK_HIP(export_gather(net->row_ptr, net->outdeg, syn_ptr(net), net->compact, net->ctab, net->dmin, d_rows, n_rows,
                               d_off, d_col, d_wb, d_del, s));
     std::vector<uint32_t> hc(tot), hw(tot);
     std::vector<uint8_t> hd(tot);
