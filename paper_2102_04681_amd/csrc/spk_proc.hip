@@ -286,33 +286,40 @@ __global__ __launch_bounds__(kProcThreads) void k_push_proc(StepArgs a, uint32_t
 // Rows generated once (the graph path's default for procedural networks).
 // Between the push and the tile kernels lies a kernel boundary, so pages
 // need not stay on one XCD: push block b of NBLK (= pg1, one per compute
-// unit) takes the b-th equal share of the step's spikes, generates every
-// synapse of their rows once (no group filter: an eighth of the target draws
-// of k_push_proc) and files each event into its own page of the target's
+// unit) takes the b-th equal share of the synapses of the step's spikes (its
+// first and last rows may be parts of rows), generates each once (no group
+// filter: an eighth of the target draws of k_push_proc) and files each event into its own page of the target's
 // tile, page (group of the tile, b, arrival slot, tile of the group); the
 // tile kernel drains the pages of all NBLK push blocks.  Each lane generates
 // consecutive synapses of the block's share (the wave's slice), kOnceR per
 // window, with the target, delay and weight streams' prefixes of the lane's
 // row held in registers; the events are sorted by (delay index, tile) over
 // all T tiles of the network, as k_push_proc does within a group.
+//
+// A window costs the scan of all buckets, the barriers and a round of stores
+// whatever it holds, and the slowest block sets the time.  Shares of whole
+// rows gave some blocks a row more, and with it a second window for a few
+// hundred synapses (2e6 neurons, fan-out 1,500: 8 or 9 rows, 12,000 or 13,500
+// synapses, at 12,288 per window); equal shares of about 12,060 fit one
+// window of 14,336.
 constexpr uint32_t kOnceChunk = 256;  // spikes per chunk
 
 template <bool CMP>
 struct OnceLDS {
     using Rec = typename SynRec<CMP>::T;
-    static constexpr int R = CMP ? 12 : 6;                    // events per lane per window
+    static constexpr int R = CMP ? 14 : 7;                    // events per lane per window
     static constexpr uint32_t kWin = R * kProcThreads;
+    static_assert(kWin <= 65535, "bucket starts are 16 bits wide");
     Rec stage[kWin];                 // bucket-sorted events {bucket << 16 | page record}
     uint32_t sid[kOnceChunk];        // the chunk's spikes (kNoSpike: an ID out of range)
     uint32_t pre[kMaxTiles + 1];     // prefix of the source tiles' spike counts
     uint32_t bcnt[kOnceMaxB];        // events per bucket in this window, then rank cursor
-    uint32_t bst[kOnceMaxB];         // bucket starts in the stage
+    uint16_t bst[kOnceMaxB];         // bucket starts in the stage
     uint32_t wb[kOnceMaxB];          // page position of stage entry q is wb[b] + q
     uint32_t fill[kOnceMaxB];        // records already in the bucket's page
     uint32_t pidx[kOnceMaxB];        // page of the bucket
     uint32_t more[kProcWaves];       // the wave has synapses left to generate
     uint32_t ws[16];
-    unsigned long long ws64[16];
 };
 
 template <bool FIXED, bool CMP>
@@ -341,12 +348,13 @@ __global__ __launch_bounds__(kProcThreads) void k_push_proc_once(StepArgs a, uin
         L.bcnt[q] = 0;
     }
     const uint32_t M = dbg ? a.dbg_n : load_spike_set(a, sslot, L.pre, L.ws);
-    uint32_t k0, k1;
-    equal_share(M, b, NBLK, &k0, &k1);
+    // the share: synapses v0 .. v1 - 1 of the spikes' rows laid end to end
+    const uint64_t V_all = (uint64_t)M * kout, vq = V_all / NBLK, vr = V_all - vq * NBLK;
+    const uint64_t v0 = vq * b + vr * b / NBLK, v1 = vq * (b + 1) + vr * (b + 1) / NBLK;
+    const uint32_t k0 = kout ? (uint32_t)(v0 / kout) : 0u, k1 = kout ? (uint32_t)((v1 + kout - 1) / kout) : 0u;
     const uint64_t cap = a.page_cap;
     const bool uniform_w = !CMP && a.pr.w_uniform;
-    uint64_t emitted = 0;
-    for (uint32_t c0 = k0; c0 < k1 && kout; c0 += kOnceChunk) {
+    for (uint32_t c0 = k0; c0 < k1 && v0 < v1; c0 += kOnceChunk) {
         const uint32_t K = k1 - c0 < kOnceChunk ? k1 - c0 : kOnceChunk;
         if (tid < K) {
             const uint32_t k = c0 + tid;
@@ -356,14 +364,16 @@ __global__ __launch_bounds__(kProcThreads) void k_push_proc_once(StepArgs a, uin
             const bool bad = s >= a.n;
             if (bad && b == 0) atomicOr(a.flags, kFlagBadSpike);
             L.sid[tid] = bad ? kNoSpike : s;
-            emitted += bad ? 0u : kout;
         }
         lds_sync();
-        // the wave's slice [vb, ve) of the chunk's K * kout synapses; lane l
-        // generates synapse v = vcur + l, i.e. synapse j of spike si
-        const uint32_t V = K * kout;
-        const uint32_t vb = (uint32_t)((uint64_t)V * w / kProcWaves);
-        const uint32_t ve = (uint32_t)((uint64_t)V * (w + 1) / kProcWaves);
+        // the wave's slice [vb, ve) of the share's part [lo, lo + V) of the
+        // chunk's K * kout synapses; lane l generates synapse v = vcur + l,
+        // i.e. synapse j of spike si
+        const uint64_t cv = (uint64_t)c0 * kout;
+        const uint32_t lo = v0 > cv ? (uint32_t)(v0 - cv) : 0u;
+        const uint32_t V = (v1 - cv < (uint64_t)K * kout ? (uint32_t)(v1 - cv) : K * kout) - lo;
+        const uint32_t vb = lo + (uint32_t)((uint64_t)V * w / kProcWaves);
+        const uint32_t ve = lo + (uint32_t)((uint64_t)V * (w + 1) / kProcWaves);
         uint32_t vcur = vb;                                // (wave-uniform)
         uint32_t si = (vb + lane) / kout, j = (vb + lane) - si * kout;
         uint32_t sicur = kNoSpike, scur = kNoSpike;        // the lane's row (index, ID) and
@@ -428,7 +438,7 @@ __global__ __launch_bounds__(kProcThreads) void k_push_proc_once(StepArgs a, uin
                 for (uint32_t k = 0; k < P; k++) {
                     if (b0 + k < NB) {
                         const uint32_t bb = b0 + k, c = L.bcnt[bb], f = L.fill[bb];
-                        L.bst[bb] = ex;
+                        L.bst[bb] = (uint16_t)ex;
                         L.wb[bb] = f - ex;
                         L.fill[bb] = f + c;
                         L.bcnt[bb] = 0;
@@ -476,10 +486,8 @@ __global__ __launch_bounds__(kProcThreads) void k_push_proc_once(StepArgs a, uin
     }
     lds_sync();
     for (uint32_t q = tid; q < NB; q += kProcThreads) a.pfill[L.pidx[q]] = L.fill[q];
-    if (!dbg) {  // events emitted at t (each spike is in one block's share)
-        const uint64_t tot = block_sum_u64(emitted, L.ws64);
-        if (tid == 0 && tot) atomicAdd((unsigned long long *)&a.events8[t * kGroups], (unsigned long long)tot);
-    }
+    if (!dbg && tid == 0 && v0 < v1)  // events emitted at t
+        atomicAdd((unsigned long long *)&a.events8[t * kGroups], (unsigned long long)(v1 - v0));
 }
 
 // Rows of the given sources as generated, synapse j of row r at out_off[r] + j:
