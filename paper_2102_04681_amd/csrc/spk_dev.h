@@ -255,6 +255,14 @@ __device__ __forceinline__ float fixed64_to_float(unsigned long long acc, int32_
     return (float)ldexp((double)(long long)acc, -s64);
 }
 
+// Two packed 16-bit event counts of classes worth w0 and w1 per event (the
+// classes' accumulator units scaled by 2^-s64: products and their sum are
+// integers below 2^53 times that, so exact), rounded once as above.
+__device__ __forceinline__ float counts_to_float(uint32_t acc, double w0, double w1)
+{
+    return (float)__fma_rn((double)(acc & 0xffffu), w0, __dmul_rn((double)(acc >> 16), w1));
+}
+
 // Accumulator units of one event: the stored weight bits converted
 // (full format), or the class's precomputed value (compact format).
 template <bool FIXED>

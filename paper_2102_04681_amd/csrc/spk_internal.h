@@ -253,6 +253,10 @@ struct RunArgs {
     uint64_t t0, n_steps;   // steps [t0, t0 + n_steps)
     uint32_t R;             // workgroups per XCD
     uint32_t D;             // binned delivery: steps per batch (1 .. min(d_min, kRunMaxD))
+    // fp32 mode, binned delivery of compact records: accumulators are packed
+    // event counts (s.wval: 1 and 65536) of classes worth w0, w1 per event
+    uint32_t counts;
+    double w0, w1;
 };
 
 // Resident step kernel (spk_ring.hip): one workgroup per tile, the inputs of

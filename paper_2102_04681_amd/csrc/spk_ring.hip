@@ -183,9 +183,7 @@ __device__ __forceinline__ float ring_input(const ModelArgs &m, AccT acc, uint32
         return ldexpf((float)(s + (int32_t)K * m.ext_wq + m.bias_q), -m.shift);
     } else {
         float isyn;
-        // (w0, w1: the classes' units scaled by 2^-shift64; the products and
-        // their sum are integers below 2^53 times that, so exact)
-        if constexpr (CNT) isyn = (float)__fma_rn((double)(acc & 0xffffu), w0, __dmul_rn((double)(acc >> 16), w1));
+        if constexpr (CNT) isyn = counts_to_float(acc, w0, w1);
         else isyn = fixed64_to_float(acc, m.shift64);
         return __fadd_rn(__fadd_rn(isyn, __fmul_rn((float)K, m.ext_w)), m.i_bias);
     }

@@ -167,6 +167,7 @@ struct RunLDS {
     float mk, v_rest, v_th, v_reset, i_bias, ext_w;
     int32_t ext_wq, bias_q, shift, shift64;
     uint32_t ref_steps, pois_len;
+    double w0, w1;  // (packed event counts: what an event of each class is worth)
     // compact records: accumulator units of each weight class, read by the
     // drain with one LDS load per record instead of a chain of selects among
     // kernel arguments
@@ -397,6 +398,15 @@ __device__ bool wait_pushes(const RunArgs &ra, RunLDS<FIXED, CMP> &L, uint32_t x
     return L.stop == 0;
 }
 
+// Accumulator units of one compact page record: its class's in the LDS table;
+// packed counts: one event of class 0 or 1 (an LDS load less per record).
+template <bool FIXED, bool CMP, bool CNT>
+__device__ __forceinline__ long long drain_units(const RunLDS<FIXED, CMP> &L, uint32_t r)
+{
+    if constexpr (CNT) return (long long)(1u << ((r >> (kPageClassShift - 4)) & 16u));
+    else return L.wtab[(r >> kPageClassShift) & (kMaxClasses - 1)];
+}
+
 // Tile phase, binned delivery: sum the records of the pages of the Db
 // arrival steps t_first .. t_first + Db - 1 (one page per push block of the
 // group and step) into the LDS accumulators, those of step u at
@@ -411,7 +421,7 @@ __device__ bool wait_pushes(const RunArgs &ra, RunLDS<FIXED, CMP> &L, uint32_t x
 // dropped; only the rest of a longer page goes through the chunk tables.
 // The pages of an arrival step are not written while it is drained, so the
 // records read are the filed ones or stale ones beyond the count.
-template <bool FIXED, bool CMP, bool ONE>
+template <bool FIXED, bool CMP, bool CNT, bool ONE>
 __device__ void run_drain(const StepArgs &a, RunLDS<FIXED, CMP> &L, uint32_t x, uint32_t c, uint32_t tile,
                           uint32_t tile_n, uint32_t pslot0, uint32_t Db)
 {
@@ -491,8 +501,7 @@ __device__ void run_drain(const StepArgs &a, RunLDS<FIXED, CMP> &L, uint32_t x, 
                 for (int k = 0; k < 4; k++) {
                     // both records' units read before either add
                     const uint32_t r0 = wd[k] & 0xffffu, r1 = wd[k] >> 16;
-                    const long long u0 = L.wtab[(r0 >> kPageClassShift) & (kMaxClasses - 1)];
-                    const long long u1 = L.wtab[(r1 >> kPageClassShift) & (kMaxClasses - 1)];
+                    const long long u0 = drain_units<FIXED, CMP, CNT>(L, r0), u1 = drain_units<FIXED, CMP, CNT>(L, r1);
                     if (o + 2 * k < f) Acc<FIXED>::add(&L.u.t.acc[r0 & kPageLocalMask], u0);
                     if (o + 2 * k + 1 < f) Acc<FIXED>::add(&L.u.t.acc[r1 & kPageLocalMask], u1);
                 }
@@ -541,8 +550,7 @@ __device__ void run_drain(const StepArgs &a, RunLDS<FIXED, CMP> &L, uint32_t x, 
 #pragma unroll
                 for (int k = 0; k < 4; k++) {
                     const uint32_t r0 = wd[k] & 0xffffu, r1 = wd[k] >> 16;
-                    const long long u0 = L.wtab[(r0 >> kPageClassShift) & (kMaxClasses - 1)];
-                    const long long u1 = L.wtab[(r1 >> kPageClassShift) & (kMaxClasses - 1)];
+                    const long long u0 = drain_units<FIXED, CMP, CNT>(L, r0), u1 = drain_units<FIXED, CMP, CNT>(L, r1);
                     if ((okm >> (8 * u + 2 * k)) & 1u) Acc<FIXED>::add(&L.u.t.acc[ao + (r0 & kPageLocalMask)], u0);
                     if ((okm >> (8 * u + 2 * k + 1)) & 1u)
                         Acc<FIXED>::add(&L.u.t.acc[ao + (r1 & kPageLocalMask)], u1);
@@ -633,8 +641,8 @@ __device__ __forceinline__ bool lif_step(float &V, uint32_t &r, float I, float m
 // state and the draws in LDS (input: the accumulators from acc[aoff] on);
 // spikes compacted by wavefront ballots straight into the tile's segment of
 // the spike list of t.
-template <bool FIXED, bool CMP, bool DIRECT>
-__device__ void run_update(const RunArgs &ra, RunLDS<FIXED, CMP> &L, uint32_t x, uint32_t tile,
+template <bool FIXED, bool CMP, bool CNT, bool DIRECT>
+__device__ void run_update(const RunArgs &ra, RunLDS<FIXED || CNT, CMP> &L, uint32_t x, uint32_t tile,
                            uint32_t tile_lo, uint32_t tile_n, uint64_t t, uint32_t tslot, uint64_t delivered,
                            uint32_t aoff, uint32_t kpoff, uint32_t *cnt, uint32_t *cnt_next, bool late)
 {
@@ -646,6 +654,11 @@ __device__ void run_update(const RunArgs &ra, RunLDS<FIXED, CMP> &L, uint32_t x,
                 ext_w = L.ext_w;
     const int32_t ext_wq = L.ext_wq, bias_q = L.bias_q, shift = L.shift, shift64 = L.shift64;
     const uint32_t ref_steps = L.ref_steps, pois_len = L.pois_len;
+    double w0 = 0.0, w1 = 0.0;
+    if constexpr (CNT) {
+        w0 = L.w0;
+        w1 = L.w1;
+    }
     uint64_t ev = 0;
     uint64_t bal[kRunRounds];  // per round: the wave's firing lanes (wave-uniform)
     uint32_t nw_spk = 0;       // the wave's spikes over all rounds
@@ -666,7 +679,9 @@ __device__ void run_update(const RunArgs &ra, RunLDS<FIXED, CMP> &L, uint32_t x,
                         const int32_t qt = (int32_t)L.u.t.acc[aoff + q] + (int32_t)K * ext_wq + bias_q;
                         I = ldexpf((float)qt, -shift);
                     } else {
-                        const float isyn = fixed64_to_float(L.u.t.acc[aoff + q], shift64);
+                        float isyn;
+                        if constexpr (CNT) isyn = counts_to_float((uint32_t)L.u.t.acc[aoff + q], w0, w1);
+                        else isyn = fixed64_to_float(L.u.t.acc[aoff + q], shift64);
                         const float ext = __fmul_rn((float)K, ext_w);
                         I = __fadd_rn(__fadd_rn(isyn, ext), i_bias);
                     }
@@ -784,17 +799,22 @@ __device__ void run_update(const RunArgs &ra, RunLDS<FIXED, CMP> &L, uint32_t x,
 // run_update, and compacts each step's spikes straight into that step's
 // segment of the spike list (one counter nb[u] per step: no barrier between
 // steps).  Then one barrier, and every step's count is published.
-template <bool FIXED, bool CMP>
-__device__ void run_update_batch(const RunArgs &ra, RunLDS<FIXED, CMP> &L, uint32_t x, uint32_t tile,
+template <bool FIXED, bool CMP, bool CNT>
+__device__ void run_update_batch(const RunArgs &ra, RunLDS<FIXED || CNT, CMP> &L, uint32_t x, uint32_t tile,
                                  uint32_t tile_lo, uint32_t tile_n, uint64_t t_first, uint32_t ss, uint32_t Db)
 {
-    using AccT = typename RunLDS<FIXED, CMP>::AccT;
+    using AccT = typename RunLDS<FIXED || CNT, CMP>::AccT;
     const StepArgs &a = ra.s;
     const uint32_t tid = tid_here(), lane = tid & (kWave - 1), W = a.tl.W;
     const float mk = L.mk, v_rest = L.v_rest, v_th = L.v_th, v_reset = L.v_reset, i_bias = L.i_bias,
                 ext_w = L.ext_w;
     const int32_t ext_wq = L.ext_wq, bias_q = L.bias_q, shift = L.shift, shift64 = L.shift64;
     const uint32_t ref_steps = L.ref_steps, pois_len = L.pois_len;
+    double w0 = 0.0, w1 = 0.0;
+    if constexpr (CNT) {
+        w0 = L.w0;
+        w1 = L.w1;
+    }
     for (uint32_t q0 = 0; q0 < tile_n; q0 += kRunThreads) {  // (uniform trip count: ballots below)
         const uint32_t q = q0 + tid;
         const bool live = q < tile_n;
@@ -815,7 +835,9 @@ __device__ void run_update_batch(const RunArgs &ra, RunLDS<FIXED, CMP> &L, uint3
                 const int32_t qt = (int32_t)acc + (int32_t)K * ext_wq + bias_q;
                 I = ldexpf((float)qt, -shift);
             } else {
-                const float isyn = fixed64_to_float(acc, shift64);
+                float isyn;
+                if constexpr (CNT) isyn = counts_to_float((uint32_t)acc, w0, w1);
+                else isyn = fixed64_to_float(acc, shift64);
                 const float ext = __fmul_rn((float)K, ext_w);
                 I = __fadd_rn(__fadd_rn(isyn, ext), i_bias);
             }
@@ -1158,10 +1180,16 @@ __device__ __forceinline__ uint64_t raster_advance(const StepArgs &a, uint64_t t
 // BATCH: binned delivery of LIF neurons in batches of several steps, whose
 // updates run in registers (run_update_batch); a variant of its own, so that
 // the one-step kernels keep their register allocation.
-template <bool FIXED, bool CMP, bool DIRECT, bool BATCH>
+// CNT: fp32 mode, two weight classes or one, compact records: the tile's
+// accumulators are two 16-bit event counts in 32 bits, added to as fixed-point
+// ones are (wval: 1 and 65536, overflow accumulators included) and multiplied
+// by the classes' units in the update.  The sum is the same integer; the
+// drain's LDS atomics and the zeroing move half the bytes.
+template <bool FIXED, bool CMP, bool CNT, bool DIRECT, bool BATCH>
 __global__ __launch_bounds__(kRunThreads) void k_run(RunArgs ra)
 {
-    __shared__ RunLDS<FIXED, CMP> L;
+    constexpr bool A32 = FIXED || CNT;  // accumulators of 32 bits
+    __shared__ RunLDS<A32, CMP> L;
     const StepArgs &a = ra.s;
     RunCtl *ctl = ra.ctl;
     const uint32_t tid = threadIdx.x;
@@ -1181,6 +1209,8 @@ __global__ __launch_bounds__(kRunThreads) void k_run(RunArgs ra)
         L.shift64 = mm.shift64;
         L.ref_steps = mm.ref_steps;
         L.pois_len = mm.pois_len;
+        L.w0 = ra.w0;
+        L.w1 = ra.w1;
         for (uint32_t k = 0; k < kMaxClasses; k++) L.wtab[k] = a.wval[k];
         const uint32_t raw = xcc_id();
         const uint32_t x = raw & (kGroups - 1);
@@ -1277,13 +1307,13 @@ __global__ __launch_bounds__(kRunThreads) void k_run(RunArgs ra)
             // binned: every push block of the XCD has filed the previous batch
             if (!DIRECT && !wait_pushes(ra, L, x, ex)) return;
             if (!DIRECT) {  // all steps of the batch
-                if (!BATCH && Db == 1) run_drain<FIXED, CMP, true>(a, L, x, r, tile, tile_n, ps, 1);
-                else run_drain<FIXED, CMP, false>(a, L, x, r, tile, tile_n, ps, Db);
+                if (!BATCH && Db == 1) run_drain<A32, CMP, CNT, true>(a, L, x, r, tile, tile_n, ps, 1);
+                else run_drain<A32, CMP, CNT, false>(a, L, x, r, tile, tile_n, ps, Db);
             }
             bool batched = false;
             if constexpr (BATCH) {
                 batched = lif && Db > 1;
-                if (batched) run_update_batch(ra, L, x, tile, tile_lo, tile_n, t_first, ss, Db);
+                if (batched) run_update_batch<FIXED, CMP, CNT>(ra, L, x, tile, tile_lo, tile_n, t_first, ss, Db);
             }
             late = !DIRECT && !batched;
             if (!batched) for (uint32_t u = 0; u < Db; u++) {
@@ -1294,7 +1324,7 @@ __global__ __launch_bounds__(kRunThreads) void k_run(RunArgs ra)
                 }
                 const uint32_t tslot = ss + u < a.spk_slots ? ss + u : ss + u - a.spk_slots;
                 const uint64_t delivered = DIRECT ? run_gather(a, L, tile, tile_lo, t, tslot) : L.u.t.dlv[u];
-                run_update<FIXED, CMP, DIRECT>(ra, L, x, tile, tile_lo, tile_n, t, tslot, delivered, u * tl.W,
+                run_update<FIXED, CMP, CNT, DIRECT>(ra, L, x, tile, tile_lo, tile_n, t, tslot, delivered, u * tl.W,
                                                lif ? u * tl.W : 0u, &L.nspk2[u & 1u], &L.nspk2[(u + 1u) & 1u],
                                                late && u + 1 == Db);
             }
@@ -1353,29 +1383,31 @@ __global__ __launch_bounds__(kRunThreads) void k_run(RunArgs ra)
     if (tid == 0 && x == 0 && r == 0) *(uint64_t *)a.t_base = ra.t0 + ra.n_steps;
 }
 
-template <bool FIXED, bool CMP, bool DIRECT, bool BATCH>
+template <bool FIXED, bool CMP, bool CNT, bool DIRECT, bool BATCH>
 hipError_t launch_run_t(const RunArgs &ra, hipStream_t s)
 {
     RunArgs arg = ra;
     void *args[] = {&arg};
-    return hipLaunchCooperativeKernel((const void *)k_run<FIXED, CMP, DIRECT, BATCH>, dim3(kGroups * ra.R),
+    return hipLaunchCooperativeKernel((const void *)k_run<FIXED, CMP, CNT, DIRECT, BATCH>, dim3(kGroups * ra.R),
                                       dim3(kRunThreads), args, 0, s);
 }
 
-template <bool FIXED, bool CMP>
+template <bool FIXED, bool CMP, bool CNT = false>
 hipError_t launch_run_fc(const RunArgs &ra, hipStream_t s)
 {
 #if SPK_RUN_BATCH
-    return launch_run_t<FIXED, CMP, false, true>(ra, s);
+    return launch_run_t<FIXED, CMP, CNT, false, true>(ra, s);
 #else
-    if (ra.s.direct) return launch_run_t<FIXED, CMP, true, false>(ra, s);
-    return launch_run_t<FIXED, CMP, false, false>(ra, s);
+    if constexpr (!CNT)
+        if (ra.s.direct) return launch_run_t<FIXED, CMP, false, true, false>(ra, s);
+    return launch_run_t<FIXED, CMP, CNT, false, false>(ra, s);
 #endif
 }
 
 hipError_t launch_run_any(const RunArgs &ra, hipStream_t s)
 {
     const bool F = ra.s.m.fixed, C = ra.s.compact;
+    if (ra.counts) return launch_run_fc<false, true, true>(ra, s);
     if (F && C) return launch_run_fc<true, true>(ra, s);
     if (F && !C) return launch_run_fc<true, false>(ra, s);
     if (!F && C) return launch_run_fc<false, true>(ra, s);
@@ -1413,6 +1445,7 @@ hipError_t launch_run(const RunArgs &ra, hipStream_t s)
     const StepArgs &a = ra.s;
     if (a.compact ? !a.syn32 || (!a.direct && !a.pages16) : !a.syn || (!a.direct && !a.pages))
         return hipErrorInvalidValue;
+    if (ra.counts && (a.m.fixed || !a.compact || a.direct)) return hipErrorInvalidValue;
     if (!a.direct && ra.D > 1 && a.m.kind != SPK_SOURCE) return launch_run_batched(ra, s);
     return launch_run_any(ra, s);
 }

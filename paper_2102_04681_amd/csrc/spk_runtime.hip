@@ -287,6 +287,7 @@ struct spk_net {
     bool persistent = false;
     uint32_t run_R = 0;
     uint32_t run_D = 1;  // persistent kernel, binned delivery: steps per batch
+    bool run_counts = false;  // persistent kernel: accumulators are packed event counts
     RunCtl *ctl = nullptr;
     // resident step kernel: planned before the rows are laid out (the tiling
     // and the per-tile row offsets depend on it), used if it can be launched
@@ -955,9 +956,11 @@ spk_status finish_rows(spk_net *net)
         net->shift64 = std::max(0, std::min(100, 52 - e));
     }
     class_units(net);
-    if (net->ring_counts && net->P.conn_kind != SPK_CONN_EXPLICIT &&
-        (m / std::max<uint64_t>(1, std::min(net->ctab.abs[0], net->ctab.abs[1])) > 65535 ||
-         !net->ctab.abs[0] || !net->ctab.abs[1])) {
+    // no neuron can receive 2^16 events of a class in one step (an in-synapse
+    // delivers at most one): m bounds each class's count times its |weight|
+    const uint64_t abs_min = net->compact && net->n_cls <= 2 ? std::min(net->ctab.abs[0], net->ctab.abs[1]) : 0;
+    const bool counts_fit = abs_min && m / abs_min <= 65535;
+    if (net->ring_counts && net->P.conn_kind != SPK_CONN_EXPLICIT && !counts_fit) {
         // a neuron could receive 2^16 events of a class: sums, where they fit
         net->ring_counts = false;
         if (net->lists > 1 || (uint64_t)net->dmax * net->tl.W * ring_acc_bytes(fixed, false) > kRingBytes) net->ring = false;
@@ -967,6 +970,8 @@ spk_status finish_rows(spk_net *net)
     // to the smallest delay, so that nothing a batch files arrives within it,
     // and within the bucket, slot and LDS limits.
     const Tiling &tl = net->tl;
+    // (fixed-point sums are 32 bits wide already)
+    net->run_counts = counts_fit && !fixed && !net->direct && !net->proc;
     net->run_D = 1;
     if (!net->direct || (net->ring && net->P.delivery != SPK_DELIVERY_DIRECT)) {
         // Default at most 8 steps: longer batches save hand-offs but give a
@@ -1234,6 +1239,12 @@ RunArgs run_args(const spk_net *net, uint64_t t0, uint64_t n_steps)
     ra.n_steps = n_steps;
     ra.R = net->run_R;
     ra.D = net->direct ? 1u : net->run_D;
+    if (net->run_counts) {
+        ra.counts = 1u;
+        ra.w0 = std::ldexp((double)net->wval[0], -net->shift64);
+        ra.w1 = std::ldexp((double)net->wval[1], -net->shift64);
+        for (uint32_t k = 0; k < kMaxClasses; k++) ra.s.wval[k] = k == 0 ? 1 : k == 1 ? 65536 : 0;
+    }
     return ra;
 }
 
