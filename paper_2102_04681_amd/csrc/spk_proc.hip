@@ -301,7 +301,8 @@ __global__ __launch_bounds__(kProcThreads) void k_push_proc(StepArgs a, uint32_t
 // rows gave some blocks a row more, and with it a second window for a few
 // hundred synapses (2e6 neurons, fan-out 1,500: 8 or 9 rows, 12,000 or 13,500
 // synapses, at 12,288 per window); equal shares of about 12,060 fit one
-// window of 14,336.
+// window of 14,336: 52.5 -> 51.2 us per step.  What bounds the kernel is its
+// scattered page stores, about 1.2e6 lines of five bytes each per step.
 constexpr uint32_t kOnceChunk = 256;  // spikes per chunk
 
 template <bool CMP>

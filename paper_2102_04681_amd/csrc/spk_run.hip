@@ -1184,7 +1184,9 @@ __device__ __forceinline__ uint64_t raster_advance(const StepArgs &a, uint64_t t
 // accumulators are two 16-bit event counts in 32 bits, added to as fixed-point
 // ones are (wval: 1 and 65536, overflow accumulators included) and multiplied
 // by the classes' units in the update.  The sum is the same integer; the
-// drain's LDS atomics and the zeroing move half the bytes.
+// drain's LDS atomics and the zeroing move half the bytes, and a record's
+// unit is a shift instead of an LDS load (2e6 neurons, 3e9 synapses: 24.89 ->
+// 24.34 us per step; with the unit from the table 24.7).
 template <bool FIXED, bool CMP, bool CNT, bool DIRECT, bool BATCH>
 __global__ __launch_bounds__(kRunThreads) void k_run(RunArgs ra)
 {
