@@ -63,11 +63,7 @@ __device__ __forceinline__ void put_syn(const ConnArgs &c, void *syn, uint64_t e
 {
     if (c.compact) {
         uint32_t cls = src < c.n_exc ? 0u : 1u;
-        if (c.kind == SPK_CONN_EXPLICIT) {
-            cls = 0;
-            for (uint32_t k = 1; k < kMaxClasses; k++)
-                if (c.cls_w[k] == __float_as_uint(w)) cls = k;
-        }
+        if (c.kind == SPK_CONN_EXPLICIT) cls = weight_class(c.cls_w, __float_as_uint(w));
         ((uint32_t *)syn)[e] = (cls << kClassShift) | (j << kTargetBits) | tgt;
     } else {
         ((int2 *)syn)[e] = make_syn(j, tgt, weight_bits(c, w));

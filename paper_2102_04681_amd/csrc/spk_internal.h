@@ -33,6 +33,17 @@ constexpr uint32_t kClassShift = 30;
 __host__ __device__ __forceinline__ uint32_t rec_target(uint32_t x) { return x & kTargetMask; }
 __host__ __device__ __forceinline__ uint32_t rec_delay(uint32_t x) { return (x >> kTargetBits) & kDelayMask; }
 __host__ __device__ __forceinline__ uint32_t rec_class(uint32_t x) { return x >> kClassShift; }
+// Class of an explicit synapse's weight bits: the first of the table that has
+// them.  Unused entries repeat class 0's, and kernels that count events per
+// class (packed counts) rely on a network of at most two weights storing
+// classes 0 and 1 only.
+__host__ __device__ __forceinline__ uint32_t weight_class(const uint32_t *cls_w, uint32_t bits)
+{
+    uint32_t cls = 0;
+    for (uint32_t k = kMaxClasses; k-- > 0;)
+        if (cls_w[k] == bits) cls = k;
+    return cls;
+}
 __host__ __device__ __forceinline__ uint32_t rec_key(int2 r) { return (uint32_t)r.x; }
 __host__ __device__ __forceinline__ uint32_t rec_key(uint32_t r) { return r; }
 

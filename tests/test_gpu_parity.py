@@ -796,7 +796,7 @@ def _random_csr(n, n_w, seed):
     return row_ptr, col, w, delay
 
 
-@pytest.mark.parametrize("n_w", [1, 3, 4, 5, 0], ids=["1w", "3w", "4w", "5w", "perw"])
+@pytest.mark.parametrize("n_w", [1, 2, 3, 4, 5, 0], ids=["1w", "2w", "3w", "4w", "5w", "perw"])
 @pytest.mark.parametrize("fmt", [0, 1, 2], ids=["auto", "full", "compact"])
 def test_explicit_adjacency_formats(spk, n_w, fmt):
     n = 3000

@@ -57,3 +57,34 @@ def test_packed_counts_bit_identical(spk, name, mk, cap, monkeypatch):
     assert out[0][0].sum() > 0
     for a, b, what in zip(*out, ("counts", "events", "delivered", "v", "ref", "offsets", "ids")):
         assert np.array_equal(a, b), what
+
+
+@pytest.mark.parametrize("n_w", [1, 2])
+@pytest.mark.parametrize("delays", [(1, 3), (3, 5)], ids=["steps", "batches"])
+@pytest.mark.parametrize("cap", [None, "16"], ids=["pages", "full-pages"])
+def test_packed_counts_of_an_explicit_adjacency(spk, n_w, delays, cap, monkeypatch):
+    # the classes of an explicit adjacency's weights are 0 and 1 in order of
+    # first appearance, whichever comes first in a row, in the pages and past
+    # them
+    if cap:
+        monkeypatch.setenv("SPK_PAGE_CAP", cap)
+    n, k, T = 900, 120, 40
+    rng = np.random.default_rng(n_w)
+    row_ptr = np.arange(n + 1, dtype=np.uint64) * k
+    col = rng.integers(0, n, n * k, dtype=np.uint32)
+    w = np.array([0.02, -0.05][:n_w], np.float32)[rng.integers(0, n_w, n * k)]
+    d = rng.integers(delays[0], delays[1] + 1, n * k).astype(np.uint8)
+    cfg = I.explicit_params(n, v0_lo=-49.0, v0_hi=-49.0, t_ref_ms=0.0, i_bias=0.06, delay_min=delays[0],
+                            delay_max=delays[1], delivery=2, syn_format=2)
+    out = []
+    for mode in (1, 2):
+        g = spk.Net(dict(cfg, step_mode=mode), max_steps=T, csr=(row_ptr, col, w, d))
+        assert g.stats()["step_mode"] == mode and g.stats()["page_cap"] > 0
+        g.step(17)
+        g.step(T - 17)
+        v, r = g.state()
+        out.append([g.spike_counts(), g.events(), g.delivered(), v.view(np.uint32), r])
+        g.close()
+    assert out[0][0].sum() > 0
+    for a, b, what in zip(*out, ("counts", "events", "delivered", "v", "ref")):
+        assert np.array_equal(a, b), what

@@ -103,6 +103,30 @@ def test_null_safety():
     assert L.spk_preset(7, 0, 0.0, 1, C.byref(spk.spk_params())) == spk.SPK_EINVAL
 
 
+def _host_program(tmp_path, body):
+    """Output of a C++ program that includes the kernels' shared header."""
+    src, exe = tmp_path / "probe.cpp", tmp_path / "probe"
+    src.write_text('#include <cstdio>\n#include <cstring>\n#include "spk_internal.h"\nusing namespace spk;\n' + body)
+    subprocess.check_call(["g++", "-std=c++17", "-O2", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                           "-I" + os.path.join(ROOT, "include"),
+                           "-I" + os.path.join(ROOT, "paper_2102_04681_amd", "csrc"), str(src), "-o", str(exe)])
+    return subprocess.check_output([str(exe)], text=True)
+
+
+def test_explicit_weights_are_stored_by_their_first_class(tmp_path):
+    # a table of n distinct weights whose unused entries repeat the first
+    out = _host_program(tmp_path, """
+int main() {
+    const uint32_t w[kMaxClasses] = {0x3f800000u, 0xbf800000u, 0u, 0x80000000u};
+    for (uint32_t n = 1; n <= kMaxClasses; n++) {
+        uint32_t t[kMaxClasses];
+        for (uint32_t k = 0; k < kMaxClasses; k++) t[k] = w[k < n ? k : 0];
+        for (uint32_t k = 0; k < n; k++) printf("%u ", weight_class(t, w[k]));
+    }
+}""")
+    assert out.split() == "0 0 1 0 1 2 0 1 2 3".split()
+
+
 def test_kernel_reciprocal_divisions_are_exact():
     # The persistent kernel replaces two run-time divisions by multiplies
     # with precomputed reciprocals; both are exact over the operand ranges
