@@ -284,6 +284,51 @@ struct RingCtl {
     uint64_t box[2][kRingMaxT * kRingBoxStride];  // per batch parity and tile
     uint32_t abort_flag, pad[kCtlStride - 1];
 };
+// Which spikes of a batch a lane delivers.  A wave serves the tiles w, w + 16,
+// ... (Tn >= 16 tiles: lp lanes each), or, with fewer, tile w % Tn shared by
+// the waves w, w + Tn, ...
+constexpr uint32_t kRingWaves = 16;
+struct RingShare {
+    uint32_t tile;         // the lane's tile
+    uint32_t i0, step;     // its first spike of the tile, and the distance to the next
+    uint32_t part, parts;  // the wave's part of its tile's spikes
+    bool mine;
+};
+__host__ __device__ __forceinline__ RingShare ring_share(uint32_t Tn, uint32_t w, uint32_t lane)
+{
+    RingShare h;
+    if (Tn >= kRingWaves) {
+        uint32_t lp = kWave;  // lanes per tile (uniform)
+        while ((kWave / lp) * kRingWaves < Tn) lp >>= 1;
+        const uint32_t l = lane / lp;
+        h.tile = w + kRingWaves * l;
+        h.mine = h.tile < Tn;
+        h.i0 = lane & (lp - 1u);
+        h.step = lp;
+        h.part = 0;
+        h.parts = 1;
+    } else {
+        const uint32_t q = kRingWaves / Tn, part = w / Tn;  // waves per tile
+        h.tile = w - part * Tn;
+        h.mine = part < q;
+        h.i0 = part * kWave + lane;
+        h.step = q * kWave;
+        h.part = part;
+        h.parts = q;
+    }
+    if (!h.mine) h.tile = 0;
+    return h;
+}
+// Whether the lane's tile has more spikes (c) than its lanes hold at one each:
+// its waves then take equal ranges (ring_range), else lane i0 spike i0.  The
+// waves of a shared tile must choose alike, so the choice depends on the tile
+// only (a choice by i0 + step < c loses and repeats spikes).
+__host__ __device__ __forceinline__ bool ring_many(const RingShare &h, uint32_t c) { return c > h.step; }
+__host__ __device__ __forceinline__ void ring_range(const RingShare &h, uint32_t c, uint32_t *n0, uint32_t *n1)
+{
+    *n0 = h.parts > 1 ? c * h.part / h.parts : 0u;
+    *n1 = h.parts > 1 ? c * (h.part + 1) / h.parts : c;
+}
 struct RingArgs {
     StepArgs s;
     RingCtl *ctl;

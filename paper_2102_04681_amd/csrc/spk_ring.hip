@@ -72,6 +72,7 @@ constexpr uint32_t kIdBits = 28;                      // step of the batch << 24
 constexpr uint64_t kIdMask = (1ull << kIdBits) - 1;
 constexpr uint64_t kBegMask = (1ull << 48) - 1;
 static_assert(kRT == kBlockThreads, "the block-wide helpers assume workgroups of kBlockThreads");
+static_assert(kRW == kRingWaves, "ring_share deals the tiles to the waves");
 static_assert(kRingMaxT <= kRW * 16, "a wave serves at most 16 tiles, four lanes each");
 
 // Mailbox words.  a: spike 0 << 36 | count << 18 | 18-bit stamp (count <=
@@ -309,42 +310,6 @@ __device__ __forceinline__ void ring_gather1(const StepArgs &a, L_ &L, uint32_t 
     }
 }
 
-// Several tiles: the lane's part of the spikes.  The wave's tiles are w,
-// w + 16, ... (lane / LP of them), or, with fewer than 16 tiles, tile w % Tn
-// shared by the waves w, w + Tn, ...
-struct Share {
-    uint32_t tile;   // the lane's tile
-    uint32_t i0;     // its first spike of the tile, and the distance to the next
-    uint32_t step;
-    uint32_t part, parts;  // the wave's part of its tile's spikes
-    bool mine;
-};
-__device__ __forceinline__ Share ring_share(uint32_t Tn, uint32_t w, uint32_t lane)
-{
-    Share h;
-    if (Tn >= kRW) {
-        uint32_t lp = kWave;  // lanes per tile (uniform)
-        while ((kWave / lp) * kRW < Tn) lp >>= 1;
-        const uint32_t l = lane / lp;
-        h.tile = w + kRW * l;
-        h.mine = h.tile < Tn;
-        h.i0 = lane & (lp - 1u);
-        h.step = lp;
-        h.part = 0;
-        h.parts = 1;
-    } else {
-        const uint32_t q = kRW / Tn, part = w / Tn;  // waves per tile
-        h.tile = w - part * Tn;
-        h.mine = part < q;
-        h.i0 = part * kWave + lane;
-        h.step = q * kWave;
-        h.part = part;
-        h.parts = q;
-    }
-    if (!h.mine) h.tile = 0;
-    return h;
-}
-
 // Deliver the wave's spikes (the mailboxes of the lanes' tiles have arrived)
 // into the ring.  Few spikes: one or two per lane, as the lanes hold them.
 // More: the tiles' spikes as one sequence in tile order, up to kMany * 64 at a
@@ -357,7 +322,7 @@ __device__ __forceinline__ Share ring_share(uint32_t Tn, uint32_t w, uint32_t la
 // neurons, 1 spike per tile: 6.3 against 5.5 us).
 template <bool FIXED, bool CMP, bool CNT, class L_>
 __device__ __forceinline__ void ring_gather(const StepArgs &a, L_ &L, uint32_t tile, uint32_t w, uint32_t lane,
-                                            const Share &h, Box box, const uint32_t *seg0, uint32_t seg_cap,
+                                            const RingShare &h, Box box, const uint32_t *seg0, uint32_t seg_cap,
                                             uint32_t slot0)
 {
     const uint32_t c = h.mine ? box_cnt(box) : 0u, i = h.i0;
@@ -371,7 +336,7 @@ __device__ __forceinline__ void ring_gather(const StepArgs &a, L_ &L, uint32_t t
         // rows of equal length start at a multiple of it; no load then
         *beg = row_len ? (uint64_t)s * row_len : a.row_ptr[s];
     };
-    if (!__ballot(i + h.step < c)) {
+    if (!__ballot(ring_many(h, c))) {
         const bool in = i < c;
         if (!__ballot(in)) return;  // (several waves share the tile)
         uint32_t id = box_spike(box, i);
@@ -388,7 +353,8 @@ __device__ __forceinline__ void ring_gather(const StepArgs &a, L_ &L, uint32_t t
     uint32_t id[kMany], at[kMany], base = 0;
     // the first lane of each tile: its spikes are positions pre .. pre + n - 1
     const bool first = h.mine && (h.i0 & (kWave - 1u)) == 0;
-    const uint32_t n0 = h.parts > 1 ? c * h.part / h.parts : 0u, n1 = h.parts > 1 ? c * (h.part + 1) / h.parts : c;
+    uint32_t n0, n1;
+    ring_range(h, c, &n0, &n1);
     const uint32_t n = first ? n1 - n0 : 0u;
     const uint32_t inc = wave_scan_incl_u32(n), pre = inc - n;
     const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
@@ -528,7 +494,7 @@ __global__ __launch_bounds__(kRT) void k_ring(RingArgs)
     uint32_t e = ring_kargs().e0;
     const uint32_t dm = ring_kargs().s.dmin % pslots;
 
-    const Share share = ring_share(Tn, w, lane);
+    const RingShare share = ring_share(Tn, w, lane);
     // where the events of a batch whose first step is in slot p are filed from
     auto file_slot = [&](uint32_t p) { return p + dm < pslots ? p + dm : p + dm - pslots; };
     if (tid == 0) L.stop = 0;

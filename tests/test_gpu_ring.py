@@ -139,3 +139,73 @@ def test_resident_network_deliveries_match_oracle(spk, mk):
         for delay in (0, cfg["delay_max"]):
             want = o.deliver(spikes, delay=delay, fixed=True)[1]
             assert np.array_equal(g.debug_deliver(spikes, delay=delay).astype(np.int64), want)
+
+
+def _hub_csr(n, tiles, c, delays, w_hub, w_rest, fan):
+    """Neuron 0 drives c spikes out of every tile's neurons, the first 512 of
+    them delays[0] steps after its first spike, the rest at delays[1]; every
+    neuron has fan weak synapses to random targets."""
+    rng = np.random.default_rng(c)
+    width = n // tiles
+    first, rest = min(c, width), c - min(c, width)
+    base = np.arange(tiles)[:, None] * width
+    hub_a, hub_b = (base + np.arange(first)).ravel(), (base + np.arange(rest)).ravel()
+    col = np.concatenate([hub_a, hub_b, rng.integers(0, n, n * fan)]).astype(np.uint32)
+    d = np.concatenate([np.full(len(hub_a), delays[0]), np.full(len(hub_b), delays[1]),
+                        rng.integers(delays[0], delays[1] + 1, n * fan)]).astype(np.uint8)
+    w = np.full(len(col), w_rest, np.float32) if w_rest else \
+        rng.uniform(1e-4, 4e-4, len(col)).astype(np.float32)
+    w[: c * tiles] = w_hub
+    row_ptr = np.zeros(n + 1, np.uint64)
+    row_ptr[1:] = c * tiles + np.arange(1, n + 1, dtype=np.uint64) * fan
+    return row_ptr, col, w, d
+
+
+# tiles of 512 neurons (2 to 4: narrow because of their synapses), q = 16 // tiles
+# waves share one: batch counts per tile at the edges of 64 q .. 64 (2 q - 1)
+SHARED = [(t, c) for t in range(2, 9) for q in [16 // t]
+          for c in (64 * q, 64 * q + 1, 64 * q + 22, 96 * q, 64 * (2 * q - 1), 64 * (2 * q - 1) + 1)]
+
+
+@pytest.mark.parametrize("tiles,c", sorted(set(SHARED)))
+@pytest.mark.parametrize("kind", ["fixed", "f32", "sums"])
+def test_spikes_of_tiles_shared_by_waves(spk, tiles, c, kind):
+    # every spike's row is delivered once: V against the oracle (fixed point)
+    # and the graph path (fp32: packed counts or, with one delay, sums)
+    if kind == "sums" and c > 512:
+        pytest.skip("two delays are counted, not summed")
+    n, T = 512 * tiles, 16
+    fan = 200 if tiles > 4 else (1 << 20) // n + 60
+    delays = (5, 5) if kind == "sums" else (5, 6)
+    csr = _hub_csr(n, tiles, c, delays, 12.0, 0.0 if kind == "sums" else 2.0 ** -12, fan)
+    cfg = I.explicit_params(n, v0_lo=-49.0, v0_hi=-49.0, t_ref_ms=0.0, delay_min=delays[0], delay_max=delays[1],
+                            acc_mode=I.ACC_FIXED if kind == "fixed" else I.ACC_F32)
+    g = spk.Net(cfg, max_steps=T, csr=csr)
+    st = g.stats()
+    assert st["step_mode"] == 2 and st["page_cap"] == 0 and st["tile_width"] == 512 and st["batch_steps"] == 5
+    g.step(T)
+    if kind == "fixed":
+        o = oracle.Net(cfg, csr=csr)
+        r = o.run(T)
+        v, ref = o.state()
+        want = [r["counts"], r["events"], r["delivered"], v.view(np.uint32), ref]
+    else:
+        h = spk.Net(dict(cfg, step_mode=1), max_steps=T, csr=csr)
+        h.step(T)
+        want = _records(h, raster=False)
+    assert want[0][5:10].sum() == c * tiles  # the second batch's spikes
+    _same(_records(g, raster=False), want, f"{tiles} tiles, {c} spikes each")
+
+
+@pytest.mark.parametrize("n,rate", [(2500, 50.0), (4000, 40.0), (1100, 110.0)])
+def test_sources_in_batches_on_few_tiles(spk, n, rate):
+    # (per tile and batch about 205, 164 and, on 3 tiles, 450 spikes)
+    cfg = I.scaled(3, n, k_out=1000 if n < 2048 else 300, rate_hz=rate, delay_min=15, delay_max=15)
+    out = []
+    for mode in (0, 1):
+        g = spk.Net(dict(cfg, step_mode=mode), max_steps=64)
+        g.step(64)
+        out.append(_records(g, raster=False))
+        if mode == 0:
+            assert g.stats()["page_cap"] == 0 and g.stats()["batch_steps"] == 8
+    _same(*out, f"{n} sources")

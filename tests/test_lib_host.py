@@ -127,6 +127,56 @@ int main() {
     assert out.split() == "0 0 1 0 1 2 0 1 2 3".split()
 
 
+def test_every_spike_of_a_batch_has_one_lane(tmp_path):
+    # the resident kernel's split of the tiles' spikes over waves and lanes,
+    # as a wave decides it (the choice is the whole wave's): every spike of
+    # every tile once, for every number of tiles; shared tiles at every count
+    # up to a tile's largest batch, others at mixed counts
+    out = _host_program(tmp_path, """
+#include <cstdlib>
+#include <vector>
+static std::vector<std::vector<uint16_t>> hit;
+static bool covered(uint32_t Tn, const std::vector<uint32_t> &c) {
+    for (uint32_t t = 0; t < Tn; t++) hit[t].assign(c[t], 0);
+    for (uint32_t w = 0; w < kRingWaves; w++) {
+        RingShare h[kWave];
+        bool many = false;
+        for (uint32_t l = 0; l < kWave; l++) {
+            h[l] = ring_share(Tn, w, l);
+            if (h[l].tile >= Tn) return false;
+            many |= h[l].mine && ring_many(h[l], c[h[l].tile]);
+        }
+        for (uint32_t l = 0; l < kWave; l++) {
+            const uint32_t t = h[l].tile;
+            if (!h[l].mine) continue;
+            uint32_t n0 = h[l].i0, n1 = n0 + 1;
+            if (many) {  // the tile's first lane stands for its range
+                if (h[l].i0 % kWave) continue;
+                ring_range(h[l], c[t], &n0, &n1);
+            }
+            for (uint32_t i = n0; i < n1 && i < c[t]; i++) hit[t][i]++;
+        }
+    }
+    for (uint32_t t = 0; t < Tn; t++)
+        for (uint16_t x : hit[t])
+            if (x != 1) return false;
+    return true;
+}
+int main() {
+    hit.resize(kRingMaxT);
+    for (uint32_t Tn = 1; Tn < kRingWaves; Tn++)
+        for (uint32_t c = 0; c <= kMaxTileW; c += c < 1100 ? 1 : 61)
+            if (!covered(Tn, std::vector<uint32_t>(Tn, c))) printf("tiles %u spikes %u\\n", Tn, c);
+    for (uint32_t Tn = 1; Tn <= kRingMaxT; Tn++)
+        for (uint32_t k = 0; k < 40; k++) {
+            std::vector<uint32_t> c(Tn);
+            for (uint32_t t = 0; t < Tn; t++) c[t] = (uint32_t)rand() % (k < 10 ? 3 : k < 25 ? 70 : 700);
+            if (!covered(Tn, c)) printf("tiles %u, mixed\\n", Tn);
+        }
+}""")
+    assert not out, out[:400]
+
+
 def test_kernel_reciprocal_divisions_are_exact():
     # The persistent kernel replaces two run-time divisions by multiplies
     # with precomputed reciprocals; both are exact over the operand ranges
