@@ -361,9 +361,10 @@ __global__ __launch_bounds__(kProcThreads) void k_push_proc_once(StepArgs a, uin
             const uint32_t k = c0 + tid;
             const uint32_t s = dbg ? a.dbg_spikes[k] : spike_at(a, L.pre, sslot, k);
             // a caller's spike list (debug delivery) is checked here: an ID
-            // out of range generates nothing and raises a flag
+            // out of range generates nothing and raises a flag (in every block
+            // whose share it is in: no block sees the whole list)
             const bool bad = s >= a.n;
-            if (bad && b == 0) atomicOr(a.flags, kFlagBadSpike);
+            if (bad) atomicOr(a.flags, kFlagBadSpike);
             L.sid[tid] = bad ? kNoSpike : s;
         }
         lds_sync();

@@ -96,6 +96,31 @@ def test_noalloc_full_size_network(env):
     g.close()
 
 
+DELIVERIES = [("auto", dict()), ("binned", dict(delivery=2)), ("procedural", dict(syn_format=3)),
+              ("direct", dict(delivery=1))]
+
+
+@pytest.mark.parametrize("where", [0, 150, 299, 300])
+@pytest.mark.parametrize("name,over", DELIVERIES, ids=[d[0] for d in DELIVERIES])
+def test_noalloc_reports_a_bad_id_wherever_it_stands(env, name, over, where):
+    # (the push blocks of a procedural network see a share of the list each)
+    torch, spk = env
+    cfg = I.scaled(4, 8000, k_out=300, **over)
+    g = spk.Net(cfg, max_steps=1)
+    good = I.spike_set(cfg["n"], 300, seed=6)
+    ids = np.insert(good, where, np.uint32(cfg["n"] + where)).astype(np.int32)
+    out = torch.zeros(cfg["n"], dtype=torch.float32, device="cuda")
+    d = torch.from_numpy(ids).cuda()
+    torch.cuda.synchronize()
+    g.deliver_noalloc(d.data_ptr(), len(ids), out.data_ptr())
+    with pytest.raises(spk.SpkError) as e:
+        g.sync()
+    assert e.value.code == spk.SPK_EINVAL
+    g.sync()
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), g.debug_deliver(good).view(np.uint32))
+    g.close()
+
+
 def test_noalloc_rejects_and_reports(env):
     torch, spk = env
     cfg = I.scaled(4, 8000, k_out=300)
