@@ -124,6 +124,26 @@ struct alignas(64) RowDesc {
 };
 static_assert(sizeof(RowDesc) == 64, "one row descriptor is 64 bytes");
 
+// Whether a device's zero area of spk_deliver_noalloc may hold something, as
+// the host knows it.  A call begins by asking whether it has to clear the area
+// first, and ends by saying whether it leaves the area at zero.  A captured
+// call runs when its graph is launched, or never: it records the clear if the
+// area may be unclean now, and changes nothing here, so an eager call before
+// the graph's first launch clears for itself.
+struct ScratchFlag {
+    bool unclean = false;
+    bool begin(bool capturing)
+    {
+        const bool clear = unclean;
+        if (!capturing) unclean = true;
+        return clear;
+    }
+    void end(bool capturing, bool zero)
+    {
+        if (!capturing) unclean = !zero;
+    }
+};
+
 // Connectivity generation parameters.
 struct ConnArgs {
     uint32_t n, n_exc;

@@ -76,7 +76,7 @@ __device__ __align__(256) uint8_t scratch_zero[kNoAllocScratchBytes];
 constexpr int kMaxDevices = 64;
 struct Scratch {
     uint8_t *pages = nullptr, *zero = nullptr;
-    bool unclean = false;  // a call's kernels were not all launched: the zero area is cleared by the next
+    ScratchFlag flag;  // a call's kernels were not all launched: the zero area is cleared by the next
 };
 std::mutex g_scratch_mu;
 Scratch g_scratch[kMaxDevices];
@@ -134,20 +134,21 @@ void stage_give(uint32_t *p)
     (void)hipHostFree(p);
 }
 
-// The device's scratch, marked unclean until scratch_done.
-Scratch scratch_take(int device)
+// The device's scratch for one call (ScratchFlag): *clear = its zero area has
+// to be cleared first.
+Scratch scratch_take(int device, bool capturing, bool *clear)
 {
+    *clear = false;
     if (device < 0 || device >= kMaxDevices) return Scratch{};
     std::lock_guard<std::mutex> lock(g_scratch_mu);
-    const Scratch x = g_scratch[device];
-    g_scratch[device].unclean = true;
-    return x;
+    *clear = g_scratch[device].flag.begin(capturing);
+    return g_scratch[device];
 }
 
-void scratch_done(int device)
+void scratch_done(int device, bool capturing, bool zero)
 {
     std::lock_guard<std::mutex> lock(g_scratch_mu);
-    g_scratch[device].unclean = false;
+    g_scratch[device].flag.end(capturing, zero);
 }
 
 uint64_t prob_threshold(double p)
@@ -1935,6 +1936,8 @@ spk_status spk_deliver_noalloc(spk_net *net, const uint32_t *d_spikes, uint64_t 
     a.dbg_j = delay ? (int32_t)(delay - net->dmin) : -1;
     a.dbg_out = d_out;  // (no spikes: the tile kernel writes zeros)
     hipError_t e = hipSuccess;
+    bool capturing = false;
+    uint32_t *zero_area = nullptr;  // binned delivery: the scratch's
     if (!net->direct) {
         // Carve the zero area: fill counters, overflow flags and overflow
         // accumulators of one arrival slot; pages of as many records as the
@@ -1953,8 +1956,13 @@ spk_status spk_deliver_noalloc(spk_net *net, const uint32_t *d_spikes, uint64_t 
         if (cap < 16)
             return fail(SPK_EOVERFLOW, "network too large for the fixed scratch of spk_deliver_noalloc (" +
                                            std::to_string(kNoAllocScratchBytes >> 20) + " MiB per device)");
-        const Scratch x = scratch_take(net->device);
+        hipStreamCaptureStatus cap_st = hipStreamCaptureStatusNone;
+        SPK_HIP(hipStreamIsCapturing(s, &cap_st));
+        capturing = cap_st != hipStreamCaptureStatusNone;
+        bool clear = false;
+        const Scratch x = scratch_take(net->device, capturing, &clear);
         if (!x.pages) return fail(SPK_ESTATE, "no scratch address for the network's device");
+        zero_area = (uint32_t *)x.zero;
         a.pfill = (uint32_t *)(x.zero + o_fill);
         a.ovf_flag = (uint32_t *)(x.zero + o_flag);
         a.acc_ovf = x.zero + o_acc;
@@ -1963,12 +1971,17 @@ spk_status spk_deliver_noalloc(spk_net *net, const uint32_t *d_spikes, uint64_t 
         a.page_cap = (uint32_t)cap;
         a.pslots = 1;
         // (a fill kernel, not a memset: usable under capture)
-        if (x.unclean) e = zero_words((uint32_t *)x.zero, kNoAllocScratchBytes / 4, s);
+        if (clear) e = zero_words(zero_area, kNoAllocScratchBytes / 4, s);
         if (e == hipSuccess && n_spikes) e = launch_push(a, 0, 0, s);
     }
     if (e == hipSuccess) e = launch_tile(a, 0, 0, s);
+    // after a failed launch the area is cleared at once, so that graphs
+    // captured before find it at zero too; where even that cannot be
+    // launched, the next call clears
+    if (zero_area)
+        scratch_done(net->device, capturing,
+                     e == hipSuccess || zero_words(zero_area, kNoAllocScratchBytes / 4, s) == hipSuccess);
     if (e != hipSuccess) return fail(SPK_EHIP, hipGetErrorString(e));
-    if (!net->direct) scratch_done(net->device);
     return SPK_OK;
 }
 

@@ -30,3 +30,47 @@ def test_networks_in_turn_leave_the_scratch_clean(monkeypatch):
             g.sync()
             want = g.debug_deliver(spikes, delay=(0, 3, 20)[turn])
             assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), (turn, k)
+
+
+@pytest.mark.parametrize("over", [dict(delivery=2), dict(syn_format=3), dict(delivery=1)],
+                         ids=["binned", "procedural", "direct"])
+def test_captured_deliveries_replayed_among_eager_ones(over, monkeypatch):
+    # the call recorded in a graph: every replay delivers what the spike list
+    # then holds, with eager calls of the same and of another network between
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2102_04681_amd import spk
+    monkeypatch.setenv("SPK_PAGE_CAP", "64")
+    stream = torch.cuda.Stream()
+    cfg = I.scaled(4, 9000, k_out=250, **over)
+    n, k = cfg["n"], 400
+    g = spk.Net(cfg, stream=stream, max_steps=1)
+    other = spk.Net(I.scaled(4, 7000, k_out=200, delivery=2), stream=stream, max_steps=1)
+    d = torch.zeros(k, dtype=torch.int32, device="cuda")
+    out = torch.zeros(n, dtype=torch.float32, device="cuda")
+    other_spikes = I.spike_set(7000, 100, seed=9)
+    other_d = torch.from_numpy(other_spikes.astype(np.int32)).cuda()
+    other_out = torch.zeros(7000, dtype=torch.float32, device="cuda")
+    other_want = other.debug_deliver(other_spikes)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        g.deliver_noalloc(d.data_ptr(), k, out.data_ptr())
+    for r in range(4):
+        spikes = I.spike_set(n, k, seed=r)
+        d.copy_(torch.from_numpy(spikes.astype(np.int32)))
+        out.fill_(7)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            graph.replay()
+        torch.cuda.synchronize()
+        want = g.debug_deliver(spikes)
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), r
+        if r % 2:
+            g.deliver_noalloc(d.data_ptr(), k, out.data_ptr())
+            g.sync()
+            assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), r
+        other.deliver_noalloc(other_d.data_ptr(), 100, other_out.data_ptr())
+        other.sync()
+        assert np.array_equal(other_out.cpu().numpy().view(np.uint32), other_want.view(np.uint32)), r

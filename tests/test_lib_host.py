@@ -177,6 +177,23 @@ int main() {
     assert not out, out[:400]
 
 
+def test_a_captured_delivery_does_not_vouch_for_the_scratch(tmp_path):
+    # begin: does the call clear the zero area first; end: it left it at zero
+    out = _host_program(tmp_path, """
+int main() {
+    ScratchFlag f;
+    printf("%d", f.begin(false)); f.end(false, true);   // clean
+    printf("%d", f.begin(false)); f.end(false, false);  // a launch failed, and the clear after it
+    printf("%d", f.begin(true)); f.end(true, true);     // captured: clears in the graph
+    printf("%d", f.begin(false)); f.end(false, true);   // eager before the graph ran: clears for itself
+    printf("%d", f.begin(false)); f.end(false, true);   // clean
+    printf("%d", f.begin(true));                        // captured and given up
+    printf("%d", f.begin(false));                       // (returns without an end: unclean)
+    printf("%d", f.begin(false));
+}""")
+    assert out == "00110001"
+
+
 def test_kernel_reciprocal_divisions_are_exact():
     # The persistent kernel replaces two run-time divisions by multiplies
     # with precomputed reciprocals; both are exact over the operand ranges
