@@ -128,6 +128,32 @@ def test_in_degree_beyond_the_packed_counts(spk, delays):
     _same(_records(g, raster=False), [r["counts"], r["events"], r["delivered"], v.view(np.uint32), ref], "hub")
 
 
+@pytest.mark.parametrize("first,second", [(40_000, 40_000), (65_535, 300), (300, 65_535), (300, 65_536), (65_536, 0)])
+@pytest.mark.parametrize("acc", [I.ACC_FIXED, I.ACC_F32], ids=["fixed", "f32"])
+def test_in_degrees_of_two_weights_about_the_packed_counts(spk, acc, first, second):
+    # that many synapses of each of two weights into neuron 5, all delivered at
+    # the same step: counts up to 2^16 - 1 of each class fit, whatever their sum
+    n = 300
+    sizes = [first // 2, first - first // 2, second // 2, second - second // 2]  # rows 0 .. 3
+    row_ptr = np.zeros(n + 1, dtype=np.uint64)
+    row_ptr[1:] = np.cumsum(sizes + [0] * (n - 4))
+    m = first + second
+    col = np.full(m, 5, dtype=np.uint32)
+    w = np.full(m, 2.0 ** -13, dtype=np.float32)
+    w[first:] = -(2.0 ** -14)
+    cfg = I.explicit_params(n, v0_lo=-49.0, v0_hi=-49.0, t_ref_ms=0.0, acc_mode=acc, delay_max=2)
+    csr = (row_ptr, col, w, np.full(m, 1, dtype=np.uint8))
+    g = spk.Net(cfg, max_steps=8, csr=csr)
+    # (several delays: no sums in the resident kernel, so it takes counts or nothing)
+    assert (g.stats()["page_cap"] == 0) == (max(first, second) <= 65_535)
+    g.step(8)
+    h = spk.Net(dict(cfg, step_mode=1), max_steps=8, csr=csr)
+    h.step(8)
+    want = _records(h, raster=False)
+    assert want[2][1] == m
+    _same(_records(g, raster=False), want, f"{first} + {second}")
+
+
 @pytest.mark.parametrize("mk", [lambda: I.scaled(4, 8000, k_out=300), lambda: I.scaled(1, 6000),
                                 lambda: I.scaled(4, 20000, k_out=50, delay_min=2, delay_max=8)],
                          ids=["delays", "one-delay", "short-rows"])
