@@ -137,7 +137,8 @@ enum { SPK_STEP_AUTO = 0, SPK_STEP_GRAPH = 1, SPK_STEP_PERSISTENT = 2 };
  *   SPK_BATCH_STEPS caps the
  *   steps per batch (1..16, default 8; spk_stats_t.batch_steps);
  *   SPK_RING=0 leaves out the steps with every pending input in LDS
- *   (spk_params.step_mode) and their tiling (the results are the same). */
+ *   (spk_params.step_mode) and their tiling, SPK_RING=64 .. 8192 (a power of
+ *   two) sets the neurons per tile there (the results are the same). */
 typedef struct {
     uint32_t abi_version;      /* must be SPK_ABI_VERSION */
     uint32_t n;

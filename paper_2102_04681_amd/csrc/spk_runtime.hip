@@ -612,8 +612,12 @@ void plan_ring(spk_net *net, uint64_t nnz_expected, const uint64_t *in_max)
     const spk_params &P = net->P;
     if (net->proc || P.step_mode == SPK_STEP_GRAPH || P.delivery == SPK_DELIVERY_BINNED) return;
     if (P.delivery == SPK_DELIVERY_DIRECT && net->lists > 1) return;
-    if (const char *e = std::getenv("SPK_RING"))
+    uint32_t knob = 0;  // tile width asked for
+    if (const char *e = std::getenv("SPK_RING")) {
+        const long v = std::strtol(e, nullptr, 10);
         if (e[0] == '0') return;
+        if (v >= 64 && v <= (long)kMaxTileW && (v & (v - 1)) == 0) knob = (uint32_t)v;
+    }
     const double n = (double)net->n, ne = (double)net->n_exc, ni = n - ne;
     // Packed counts: at most two classes, and no neuron may receive 2^16
     // events of one class in one step (each in-synapse delivers at most one).
@@ -638,34 +642,58 @@ void plan_ring(spk_net *net, uint64_t nnz_expected, const uint64_t *in_max)
     if (!counts && net->lists > 1) return;
     const uint32_t acc = ring_acc_bytes(P.acc_mode == SPK_ACC_FIXED, counts);
     // Tile width (microseconds per step on one MI355X):
-    //   one tile of up to 2,048 neurons has no hand-off: 1,000 neurons 2.5
-    //   against 3.8 on two tiles, 2,000 with fan-out 100 2.8 against 3.6; with
-    //   fan-out 1,000 one compute unit is slower at the events, 4.5 against
-    //   3.8 on four (2e6 synapses), hence the bound on the synapses;
-    //   512 neurons per tile rather than fewer: half the lanes idle in the
-    //   update costs less than more mailboxes to poll (30,000 neurons 4.8 at
-    //   512, 5.2 at 256, 6.6 at 128, 4.9 at 1,024);
-    //   at most 128 tiles (120,000 neurons: 6.2 on 118 tiles of 1,024, 7.0 on
-    //   235 of 512), but not wider than 2,048 for it (300,000: 7.9 on 147
-    //   tiles of 2,048, 8.6 on 74 of 4,096);
+    //   One tile has no hand-off, but one compute unit delivers every event:
+    //   1,000 neurons with 1,000 events per step 2.6, against 3.4 on 16 tiles;
+    //   600 sources with 5,900 events 4.0 and 3.9, with 36,000 13.1 and 5.0
+    //   (page kernel 10.3); 1,500 sources (a tile of 2,048) with 1,500 events
+    //   3.5 and 3.5, with 7,300 5.0 and 3.8.  Sources fire at a known rate.
+    //   Neurons fire at most as often as their refractory time lets them,
+    //   and then one tile is to be no slower than the page kernel (2,040
+    //   neurons at 17,800 events 8.8 against 10.3; at 2,400 3.8 against 9.1).
+    //   Batches share their hand-offs: several tiles are as fast from the
+    //   start (700 neurons with delay 15 0.9 against 1.1, 2,040 0.9 against
+    //   2.5 and, driven hard, 1.3 against 6.5).
+    //   Several: narrow ones, up to 48, spread the events over more compute
+    //   units (2,500 sources at 10 / 50 / 300 Hz 4.0 / 4.7 / 10.0 on 40 tiles
+    //   of 64, 7.2 / 18.8 / 44 on 5 of 512, 9.9 / 10.5 / 19.8 in the page
+    //   kernel); more mailboxes to poll cost more than that gives at ordinary
+    //   rates (4,000 neurons 3.8 on 32 tiles, 4.0 on 63; 30,000 4.8 on 59
+    //   tiles of 512, 5.2 on 118, 6.6 on 235);
+    //   from 512 on at most 128 tiles (120,000 neurons: 6.2 on 118 tiles of
+    //   1,024, 7.0 on 235 of 512), but not wider than 2,048 for it (300,000:
+    //   7.9 on 147 tiles of 2,048, 8.6 on 74 of 4,096);
     //   from 4e8 synapses on the gather decides, on as many compute units as
     //   there are (250,000 neurons, 1.25e9 synapses: 8.8 on 245 tiles, 10.0
     //   on 123; delay 15 and 1e9 synapses: 2.0 on 196, 2.6 on 98).
+    //   Where a tile would deliver more than 8,000 events per step, narrower
+    //   ones (sources, 5,100 per tile: 60,000 at 10 Hz 7.7 on 118 tiles, 9.0
+    //   on 235; 12,700: 20,000 at 50 Hz 10.0 on 79, 8.6 on 157); neurons, which
+    //   rarely fire that often, up to 80 tiles (20,000: 4.5 on 40 and on 79).
     const uint64_t nnz = nnz_expected;
     const bool fixed_cap = std::getenv("SPK_TILES_PER_XCD") != nullptr;
     auto fits = [&](uint32_t W) {
         return (uint64_t)net->dmax * W * acc <= (W >= net->n ? kRingBytes1 : kRingBytes);
     };
     auto tiles = [&](uint32_t W) { return (net->n + W - 1) / W; };
+    const bool source = P.neuron_kind == SPK_SOURCE;
+    const double ev = source ? (double)nnz * (double)net->src_thr * 0x1p-32  // events per step
+                             : (double)nnz / (net->ref_steps + 1.0);         // ... at most, sustained
+    const uint32_t W1 = net->n <= 1024 ? 1024 : 2048;
+    const double ev1 = !source ? 20000.0 : W1 == 1024 ? 5000.0 : 2000.0;
+    const bool batches = net->dmin > 1 && P.delivery != SPK_DELIVERY_DIRECT;
     uint32_t W = 0;
-    if (fixed_cap) {
+    if (knob) {
+        W = knob;
+    } else if (fixed_cap) {
         W = make_tiling(net->n).W;
-    } else if (net->n <= 2048 && nnz <= (1u << 20) && fits(net->n <= 1024 ? 1024 : 2048)) {
-        W = net->n <= 1024 ? 1024 : 2048;
+    } else if (net->n <= 2048 && !batches && ev <= ev1 && fits(W1)) {
+        W = W1;
     } else {
         const uint32_t most = nnz >= 400000000ull ? kRingMaxT : 128;
-        for (W = 512; W < kMaxTileW; W <<= 1)
+        for (W = 64; W < 512 && tiles(W) > 48; W <<= 1) {}
+        for (; W < kMaxTileW; W <<= 1)
             if (tiles(W) <= most || (W >= 2048 && tiles(W) <= kRingMaxT)) break;
+        while (W > 64 && ev > 8000.0 * tiles(W) && tiles(W >> 1) <= (source ? kRingMaxT : 80u)) W >>= 1;
         while (W > 64 && !fits(W)) W >>= 1;  // (narrower tiles hold more arrival steps)
     }
     if (!fits(W)) return;

@@ -60,8 +60,9 @@ CASES = [  # name, parameters, steps, tiles of the resident kernel
 
 @pytest.mark.parametrize("name,mk,T,tiles", CASES, ids=[c[0] for c in CASES])
 @pytest.mark.parametrize("acc", [I.ACC_FIXED, I.ACC_F32], ids=["fixed", "f32"])
-def test_resident_kernel_bit_identical(spk, name, mk, T, tiles, acc):
+def test_resident_kernel_bit_identical(spk, name, mk, T, tiles, acc, monkeypatch):
     cfg = dict(mk(), acc_mode=acc)
+    monkeypatch.setenv("SPK_RING", "512" if tiles > 1 else "1024" if cfg["n"] <= 1024 else "2048")
     cap = cfg["n"] * T
     g = spk.Net(cfg, max_steps=T, raster_capacity=cap)
     st = g.stats()
@@ -91,6 +92,40 @@ def test_resident_kernel_bit_identical(spk, name, mk, T, tiles, acc):
         g.step(k)
         left -= k
     _same(_records(g, raster=False), want[:5], f"{name}, many calls")
+
+
+WIDTHS = [  # parameters, neurons per tile of the resident kernel
+    (lambda: I.config(0, n=1024), 1024), (lambda: I.config(0, n=1025), 2048),
+    (lambda: I.scaled(4, 1000, k_out=300, delay_max=4), 1024),
+    (lambda: I.scaled(4, 1000, k_out=300, delay_max=4, t_ref_ms=0.0), 64),   # (may fire every step)
+    (lambda: I.scaled(4, 2000, k_out=500, delay_max=4), 2048),
+    (lambda: I.scaled(4, 1000, k_out=100, delay_min=2, delay_max=4), 64),    # (batches)
+    (lambda: I.scaled(3, 1000, k_out=300, rate_hz=10.0), 1024), (lambda: I.scaled(3, 1000, k_out=300, rate_hz=50.0), 64),
+    (lambda: I.scaled(3, 2000, k_out=300, rate_hz=3.0), 2048), (lambda: I.scaled(3, 2000, k_out=300, rate_hz=10.0), 64),
+    (lambda: I.scaled(4, 3072, k_out=50, delay_max=4), 64), (lambda: I.scaled(4, 3073, k_out=50, delay_max=4), 128),
+    (lambda: I.scaled(4, 12288, k_out=50, delay_max=4), 256), (lambda: I.scaled(4, 12289, k_out=50, delay_max=4), 512),
+    (lambda: I.scaled(4, 12289, k_out=1000, delay_max=4, t_ref_ms=0.0), 256),
+    (lambda: I.scaled(4, 65536, k_out=50, delay_max=4), 512), (lambda: I.scaled(4, 65537, k_out=50, delay_max=4), 1024),
+    (lambda: I.scaled(3, 20480, k_out=1000, rate_hz=10.0), 512), (lambda: I.scaled(3, 20480, k_out=1000, rate_hz=50.0), 128),
+    (lambda: I.scaled(4, 20480, k_out=50, delay_max=253, delay_min=190), 0),  # (its inputs do not fit)
+    (lambda: I.scaled(4, 8192, k_out=50, delay_max=253, delay_min=190), 64),  # (only in narrow tiles)
+]
+
+
+@pytest.mark.parametrize("mk,width", WIDTHS, ids=[str(k) for k in range(len(WIDTHS))])
+def test_resident_kernel_tile_width(spk, mk, width):
+    # the width that the rule takes, and the same steps as the graph path
+    cfg, T = mk(), 30
+    a, b = spk.Net(cfg, max_steps=T), spk.Net(dict(cfg, step_mode=1), max_steps=T)
+    st = a.stats()
+    if width:
+        assert st["page_cap"] == 0 and st["tile_width"] == width
+    else:
+        assert st["page_cap"] > 0
+    for g in (a, b):
+        g.step(11)
+        g.step(T - 11)
+    _same(_records(a, raster=False), _records(b, raster=False), "width")
 
 
 def test_resident_kernel_serves_one_delay_of_weights_per_synapse(spk):
@@ -187,21 +222,21 @@ def _hub_csr(n, tiles, c, delays, w_hub, w_rest, fan):
     return row_ptr, col, w, d
 
 
-# tiles of 512 neurons (2 to 4: narrow because of their synapses), q = 16 // tiles
-# waves share one: batch counts per tile at the edges of 64 q .. 64 (2 q - 1)
+# tiles of 512 neurons, q = 16 // tiles waves share one: batch counts per tile
+# at the edges of 64 q .. 64 (2 q - 1)
 SHARED = [(t, c) for t in range(2, 9) for q in [16 // t]
           for c in (64 * q, 64 * q + 1, 64 * q + 22, 96 * q, 64 * (2 * q - 1), 64 * (2 * q - 1) + 1)]
 
 
 @pytest.mark.parametrize("tiles,c", sorted(set(SHARED)))
 @pytest.mark.parametrize("kind", ["fixed", "f32", "sums"])
-def test_spikes_of_tiles_shared_by_waves(spk, tiles, c, kind):
+def test_spikes_of_tiles_shared_by_waves(spk, tiles, c, kind, monkeypatch):
     # every spike's row is delivered once: V against the oracle (fixed point)
     # and the graph path (fp32: packed counts or, with one delay, sums)
     if kind == "sums" and c > 512:
         pytest.skip("two delays are counted, not summed")
-    n, T = 512 * tiles, 16
-    fan = 200 if tiles > 4 else (1 << 20) // n + 60
+    monkeypatch.setenv("SPK_RING", "512")
+    n, T, fan = 512 * tiles, 16, 200
     delays = (5, 5) if kind == "sums" else (5, 6)
     csr = _hub_csr(n, tiles, c, delays, 12.0, 0.0 if kind == "sums" else 2.0 ** -12, fan)
     cfg = I.explicit_params(n, v0_lo=-49.0, v0_hi=-49.0, t_ref_ms=0.0, delay_min=delays[0], delay_max=delays[1],
@@ -224,9 +259,10 @@ def test_spikes_of_tiles_shared_by_waves(spk, tiles, c, kind):
 
 
 @pytest.mark.parametrize("n,rate", [(2500, 50.0), (4000, 40.0), (1100, 110.0)])
-def test_sources_in_batches_on_few_tiles(spk, n, rate):
+def test_sources_in_batches_on_few_tiles(spk, n, rate, monkeypatch):
     # (per tile and batch about 205, 164 and, on 3 tiles, 450 spikes)
-    cfg = I.scaled(3, n, k_out=1000 if n < 2048 else 300, rate_hz=rate, delay_min=15, delay_max=15)
+    monkeypatch.setenv("SPK_RING", "512")
+    cfg = I.scaled(3, n, k_out=300, rate_hz=rate, delay_min=15, delay_max=15)
     out = []
     for mode in (0, 1):
         g = spk.Net(dict(cfg, step_mode=mode), max_steps=64)
