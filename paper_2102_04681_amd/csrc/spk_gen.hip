@@ -917,6 +917,18 @@ __global__ __launch_bounds__(kSumThreads) void k_rows_abs_sum(ConnArgs c, const 
         if (sum[k]) atomicAdd(&insum[tile * W + k], sum[k]);  // (a sum is of a neuron below n)
 }
 
+// Offsets of tiles sub times as wide (the rows' order is the same): entry k of
+// a row is entry k * sub of the narrow tiles', or the row's length past them.
+__global__ __launch_bounds__(kBlock) void k_coarse_toff(const uint16_t *toff, uint64_t m, uint32_t T, uint32_t sub,
+                                                       uint32_t T1, uint16_t *out)
+{
+    const uint64_t e = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (e >= m) return;
+    const uint64_t s = e / T1;
+    const uint32_t k = (uint32_t)(e - s * T1) * sub;
+    out[e] = toff[s * (T + 1) + (k < T ? k : T)];
+}
+
 __global__ __launch_bounds__(kBlock) void k_max_u64(const uint64_t *x, uint64_t m,
                                                    unsigned long long *out)
 {
@@ -1016,6 +1028,15 @@ hipError_t gen_bern_once(const ConnArgs &c, uint64_t room, uint64_t *cursor, uin
     if (c.kind != SPK_CONN_BERNOULLI || c.tl.T > kOnceTiles || !toff) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_gen_bern_once, dim3(c.n), dim3(kBlock), 0, s, c, room, (unsigned long long *)cursor, max_row,
                        row_ptr, outdeg, toff, syn);
+    return hipGetLastError();
+}
+
+hipError_t coarse_toff(const uint16_t *toff, uint32_t n, uint32_t T, uint32_t sub, uint32_t T_out, uint16_t *out,
+                       hipStream_t s)
+{
+    const uint64_t m = (uint64_t)n * (T_out + 1), blocks = (m + kBlock - 1) / kBlock;
+    if (m == 0 || blocks > 0x7fffffffull) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_coarse_toff, dim3((uint32_t)blocks), dim3(kBlock), 0, s, toff, m, T, sub, T_out + 1, out);
     return hipGetLastError();
 }
 

@@ -389,6 +389,9 @@ hipError_t bucket_rows(const ConnArgs &c, const uint64_t *row_ptr, const void *s
 hipError_t scan_counts(const uint32_t *cnt, uint64_t m, uint64_t *out, uint64_t *block_sums,
                        uint32_t *max_count, hipStream_t s);
 size_t scan_scratch_elems(uint64_t m);
+// Tile offsets of every sub-th tile: out (T_out + 1 per row) from toff (T + 1).
+hipError_t coarse_toff(const uint16_t *toff, uint32_t n, uint32_t T, uint32_t sub, uint32_t T_out, uint16_t *out,
+                       hipStream_t s);
 hipError_t out_degree(const uint64_t *row_ptr, uint32_t n, uint32_t *outdeg, hipStream_t s);
 // Per-class values of compact synapses: the stored weight bits (fp32, or the
 // quantised int32 in fixed mode) and the |weight| term of in_abs_sum.

@@ -246,7 +246,8 @@ struct spk_net {
     Keys keys{};
     std::vector<uint64_t> pois;
     std::vector<uint16_t> guide;
-    Tiling tl{};
+    Tiling tl{};   // rows are grouped by; tiles of the step paths but the resident kernel
+    Tiling rtl{};  // tiles of the resident kernel: one or several of tl's each
     bool direct = false;
     uint32_t spk_slots = 1, pslots = 1, pg1 = 1, page_cap = 0;
     // device
@@ -266,6 +267,7 @@ struct spk_net {
     uint32_t *syn32 = nullptr;
     RowDesc *desc = nullptr;
     uint16_t *toff = nullptr;
+    uint16_t *rtoff = nullptr;  // resident kernel: the offsets of its tiles (toff itself where they are the same)
     uint32_t *outdeg = nullptr;
     float *V = nullptr;
     uint8_t *ref = nullptr;
@@ -602,8 +604,9 @@ void class_units(spk_net *net)
     }
 }
 
-// Whether the resident step kernel serves the network, and its tiling
-// (called once the synapse format is known, before rows are laid out).
+// Whether the resident step kernel serves the network, its tiling, and the
+// one that rows are grouped by (called once the synapse format is known,
+// before rows are laid out).
 // in_max: the largest in-degree per class where it is known (explicit
 // adjacency), else null.
 void plan_ring(spk_net *net, uint64_t nnz_expected, const uint64_t *in_max)
@@ -700,10 +703,17 @@ void plan_ring(spk_net *net, uint64_t nnz_expected, const uint64_t *in_max)
     const Tiling tl = tiling_of(net->n, W);
     if (tl.T > kRingMaxT) return;
     // the rows' tile offsets: 64 MB, or half the full synapses' size
-    if ((double)net->n * (tl.T + 1) * 2.0 > std::max(64e6, 4.0 * (double)nnz)) return;
+    auto room = [&](const Tiling &x) { return (double)net->n * (x.T + 1) * 2.0 <= std::max(64e6, 4.0 * (double)nnz); };
+    if (!room(tl)) return;
     net->ring = true;
     net->ring_counts = counts;
-    net->tl = tl;
+    net->rtl = tl;
+    // Rows are grouped by the general tiling, as for the other step paths,
+    // where its narrower tiles' offsets have room: deliveries of a given
+    // spike list (k_tile) then run on as many compute units as there
+    // (1,000 spikes through 20,000 neurons with fan-out 700: 10.7 us, on
+    // this kernel's 40 tiles 19.3).
+    if (net->tl.W > W || !room(net->tl)) net->tl = tl;
 }
 
 // Synapse storage of the chosen format.
@@ -712,6 +722,17 @@ spk_status alloc_syn(spk_net *net, void **p, uint64_t nnz)
     uint8_t *q = nullptr;
     SPK_TRY(dalloc(net, &q, (size_t)nnz * (net->compact ? 4 : 8)));
     *p = q;
+    return SPK_OK;
+}
+
+// The rows' tile offsets, and the resident kernel's beside them where its
+// tiles are wider.
+spk_status alloc_toff(spk_net *net)
+{
+    const size_t m = (size_t)net->n * (net->tl.T + 1);
+    const bool two = net->ring && net->rtl.W != net->tl.W;
+    SPK_TRY(dalloc(net, &net->toff, m + (two ? (size_t)net->n * (net->rtl.T + 1) : 0)));
+    net->rtoff = two ? net->toff + m : net->toff;
     return SPK_OK;
 }
 
@@ -911,7 +932,7 @@ spk_status choose_delivery(spk_net *net, RowIndex *ix)
     net->direct = direct;
     *ix = RowIndex{};
     if (direct) {
-        SPK_TRY(dalloc(net, &net->toff, (size_t)net->n * (tl.T + 1)));
+        SPK_TRY(alloc_toff(net));
         ix->toff = net->toff;
     } else {
         SPK_TRY(dalloc(net, &net->desc, net->n));
@@ -936,6 +957,9 @@ spk_status finish_rows(spk_net *net)
         SPK_HIP(out_degree(net->row_ptr, net->n, net->outdeg, s));
     }
 
+    if (net->rtoff != net->toff)
+        SPK_HIP(coarse_toff(net->toff, net->n, net->tl.T, net->rtl.W / net->tl.W, net->rtl.T, net->rtoff, s));
+
     // Accumulator range.  Fixed mode: all in-synapses of one neuron at once,
     // plus the largest Poisson count and the bias, must fit in int32.  fp32
     // mode: choose the 64-bit fixed-point unit 2^-S64 as fine as the largest
@@ -955,7 +979,10 @@ spk_status finish_rows(spk_net *net)
         SPK_TRY(abs_term(net, net->P.w_inh, &ti));
         m = (uint64_t)net->P.k_in_exc * te + (uint64_t)net->P.k_in_inh * ti;
     } else if (net->toff && !std::getenv("SPK_RANGE_PASS")) {
-        // rows grouped by tile: summed tile by tile in LDS
+        // rows grouped by tile: summed tile by tile in LDS (the resident
+        // kernel's tiles, whose runs are longer)
+        ConnArgs c = conn_args(net);
+        if (net->ring) c.tl = net->rtl;
         uint64_t *insum = nullptr, *mx = nullptr;
         SPK_TRY(dalloc(net, &insum, net->n));
         SPK_TRY(dalloc(net, &mx, 1));
@@ -963,7 +990,7 @@ spk_status finish_rows(spk_net *net)
         SPK_HIP(hipMemsetAsync(mx, 0, 8, s));
         SegTimer tm;
         SPK_HIP(tm.start(s));
-        SPK_HIP(rows_abs_sum(conn_args(net), net->row_ptr, syn_ptr(net), net->toff, net->ctab, insum, s));
+        SPK_HIP(rows_abs_sum(c, net->row_ptr, syn_ptr(net), net->ring ? net->rtoff : net->toff, net->ctab, insum, s));
         SPK_HIP(max_u64(insum, net->n, mx, s));
         SPK_HIP(tm.stop(s, &net->range_ms));
         SPK_HIP(hipMemcpyAsync(&m, mx, 8, hipMemcpyDeviceToHost, s));
@@ -1025,7 +1052,7 @@ spk_status finish_rows(spk_net *net)
     if (net->ring_counts && net->P.conn_kind != SPK_CONN_EXPLICIT && !counts_fit) {
         // a neuron could receive 2^16 events of a class: sums, where they fit
         net->ring_counts = false;
-        if (net->lists > 1 || (uint64_t)net->dmax * net->tl.W * ring_acc_bytes(fixed, false) > kRingBytes) net->ring = false;
+        if (net->lists > 1 || (uint64_t)net->dmax * net->rtl.W * ring_acc_bytes(fixed, false) > kRingBytes) net->ring = false;
     }
 
     // Steps per batch of the persistent kernel (binned delivery): up
@@ -1047,7 +1074,8 @@ spk_status finish_rows(spk_net *net)
         }
         uint32_t D = std::min<uint32_t>(net->dmin, cap);
         // the tile keeps one accumulator array per step of the batch in LDS
-        while (D > 1 && ((!net->ring && (uint64_t)(D + net->lists - 1) * tl.T8 > kRunMaxBuckets) || D * tl.W > kMaxTileW)) D--;
+        const uint32_t W = net->ring ? net->rtl.W : tl.W;
+        while (D > 1 && ((!net->ring && (uint64_t)(D + net->lists - 1) * tl.T8 > kRunMaxBuckets) || D * W > kMaxTileW)) D--;
         net->run_D = D;
     }
     // Spike lists: direct delivery reads the lists of steps t - dmax .. t - dmin
@@ -1123,7 +1151,7 @@ spk_status generate_bern_once(spk_net *net, bool *ok)
     uint32_t *mx = nullptr;
     SPK_TRY(dalloc(net, &net->row_ptr, (size_t)net->n + 1));
     SPK_TRY(dalloc(net, &net->outdeg, net->n));
-    SPK_TRY(dalloc(net, &net->toff, (size_t)net->n * (net->tl.T + 1)));
+    SPK_TRY(alloc_toff(net));
     SPK_TRY(alloc_syn(net, &syn, room));
     SPK_TRY(dalloc(net, &cursor, 1));
     SPK_TRY(dalloc(net, &mx, 1));
@@ -1147,7 +1175,7 @@ spk_status generate_bern_once(spk_net *net, bool *ok)
         dfree(net, net->toff);
         net->row_ptr = nullptr;
         net->outdeg = nullptr;
-        net->toff = nullptr;
+        net->toff = net->rtoff = nullptr;
         return SPK_OK;
     }
     if (net->compact) net->syn32 = (uint32_t *)syn;
@@ -1314,13 +1342,15 @@ RingArgs ring_args(const spk_net *net, uint64_t t0, uint64_t n_steps)
 {
     RingArgs ra{};
     ra.s = step_args(net);
+    ra.s.tl = net->rtl;
+    ra.s.toff = net->rtoff;
     ra.ctl = net->rctl;
     ra.ring = net->ring_buf;
     ra.seg = net->ring_seg;
     ra.cnts = net->ring_cnts;
     ra.t0 = t0;
     ra.n_steps = n_steps;
-    ra.Tn = (net->n + net->tl.W - 1) / net->tl.W;
+    ra.Tn = (net->n + net->rtl.W - 1) / net->rtl.W;
     ra.D = net->run_D;
     ra.seg_cap = net->seg_cap;
     ra.e0 = net->ring_epoch;
@@ -1401,7 +1431,7 @@ spk_status choose_step_mode(spk_net *net)
     net->run_R = cus > 0 && cus % (int)kGroups == 0 ? (uint32_t)(cus / (int)kGroups) : 0u;
     if (net->ring) {
         // one workgroup per tile, all resident at once
-        const Tiling &tl = net->tl;
+        const Tiling &tl = net->rtl;
         const uint32_t Tn = (net->n + tl.W - 1) / tl.W;
         const size_t bytes = (size_t)Tn * net->pslots * tl.W * ring_acc_bytes(net->P.acc_mode == SPK_ACC_FIXED, net->ring_counts);
         net->seg_cap = net->run_D * tl.W;
@@ -2124,8 +2154,8 @@ spk_status spk_stats(spk_net *net, spk_stats_t *out)
     st.fixed_shift = net->P.acc_mode == SPK_ACC_FIXED ? net->P.fixed_shift : net->shift64;
     st.k = net->k;
     st.bytes_per_synapse = net->proc ? 0.0 : net->compact ? 4.0 : 8.0;
-    st.tile_width = net->tl.W;
-    st.tiles = net->tl.T;
+    st.tile_width = net->ring ? net->rtl.W : net->tl.W;
+    st.tiles = net->ring ? net->rtl.T : net->tl.T;
     // (the resident kernel files events by arrival step right after their
     // spike, as binned delivery does; with one delay of one step, or where
     // direct delivery was asked for, a tile reads the due rows)

@@ -106,6 +106,8 @@ WIDTHS = [  # parameters, neurons per tile of the resident kernel
     (lambda: I.scaled(4, 12288, k_out=50, delay_max=4), 256), (lambda: I.scaled(4, 12289, k_out=50, delay_max=4), 512),
     (lambda: I.scaled(4, 12289, k_out=1000, delay_max=4, t_ref_ms=0.0), 256),
     (lambda: I.scaled(4, 65536, k_out=50, delay_max=4), 512), (lambda: I.scaled(4, 65537, k_out=50, delay_max=4), 1024),
+    # rows grouped by narrower tiles, and by the same where the narrower ones' offsets take more than 64 MB
+    (lambda: I.scaled(4, 120_000, k_out=20, delay_max=4), 1024), (lambda: I.scaled(4, 131_072, k_out=20, delay_max=4), 1024),
     (lambda: I.scaled(3, 20480, k_out=1000, rate_hz=10.0), 512), (lambda: I.scaled(3, 20480, k_out=1000, rate_hz=50.0), 128),
     (lambda: I.scaled(4, 20480, k_out=50, delay_max=253, delay_min=190), 0),  # (its inputs do not fit)
     (lambda: I.scaled(4, 8192, k_out=50, delay_max=253, delay_min=190), 64),  # (only in narrow tiles)
@@ -114,7 +116,8 @@ WIDTHS = [  # parameters, neurons per tile of the resident kernel
 
 @pytest.mark.parametrize("mk,width", WIDTHS, ids=[str(k) for k in range(len(WIDTHS))])
 def test_resident_kernel_tile_width(spk, mk, width):
-    # the width that the rule takes, and the same steps as the graph path
+    # the width that the rule takes, and the same steps and deliveries as the
+    # graph path's
     cfg, T = mk(), 30
     a, b = spk.Net(cfg, max_steps=T), spk.Net(dict(cfg, step_mode=1), max_steps=T)
     st = a.stats()
@@ -126,6 +129,8 @@ def test_resident_kernel_tile_width(spk, mk, width):
         g.step(11)
         g.step(T - 11)
     _same(_records(a, raster=False), _records(b, raster=False), "width")
+    spikes = I.spike_set(cfg["n"], 300, seed=1)
+    assert np.array_equal(a.debug_deliver(spikes).view(np.uint32), b.debug_deliver(spikes).view(np.uint32))
 
 
 def test_resident_kernel_serves_one_delay_of_weights_per_synapse(spk):
