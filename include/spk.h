@@ -295,8 +295,8 @@ spk_status spk_debug_deliver(spk_net *net, const uint32_t *spikes, uint64_t n_sp
  * memset and does not synchronise.  Every call on one device shares them:
  * calls that overlap on one device (any network, any stream, replays of
  * captured calls among them) race, so the caller orders them (one stream, or
- * events).  Networks with direct delivery need
- * no scratch.  Results equal spk_debug_deliver's.  Network state is not
+ * events).  Direct delivery needs no
+ * scratch.  Results equal spk_debug_deliver's.  Network state is not
  * changed.  Errors (returned at once): SPK_EINVAL (null output, bad delay,
  * n_spikes >= 2^30), SPK_EOVERFLOW (the network's tiles need more overflow
  * accumulators than the scratch holds: n rounded up to whole tiles x 8

@@ -1560,6 +1560,24 @@ void destroy_net(spk_net *net)
     delete net;
 }
 
+// Whether a given spike list is delivered faster through pages than by each
+// tile reading its runs, on a resident network's rows.  Microseconds of
+// spk_deliver_noalloc, E = 1e6 events, T tiles, about: by tile 8.5 + 900 E / T
+// (fan-out 1,500, 20,000 neurons on 157 tiles: 9.5 at 300 spikes, 21.9 at
+// 1,500, 45 at 4,000; 60,000 on 235: 9.5, 15.1, 28.8), through pages 14 + 4.3 E,
+// or 1.6 E where only one of several delays is filed (20,000: 39.3 at 4,000;
+// one delay of 20 16.4 at 1,500, 23.1 at 4,000; 60,000 23.3 at 4,000).
+bool binned_pays(const spk_net *net, uint64_t n_spikes, uint32_t delay)
+{
+    if (!net->ring || !net->compact) return false;
+    const Tiling &tl = net->tl;
+    const double E = 1e-6 * (double)n_spikes * (double)net->nnz / (double)net->n;
+    const double T = (double)((net->n + tl.W - 1) / tl.W);
+    // (its accumulators and pages of the least size have to fit the scratch)
+    const uint64_t need = (uint64_t)tl.T * tl.W * 8 + (uint64_t)kGroups * push_blocks_per_group() * tl.T8 * (4 + 16 * 2);
+    return E * (900.0 / T - (delay && net->lists > 1 ? 1.6 : 4.3)) > 5.5 && need + 65536 <= kNoAllocScratchBytes;
+}
+
 // Records of n steps, summed over the groups, after the enqueued work.
 spk_status read_groups(spk_net *net, const void *dev, size_t elem, uint64_t t0, uint64_t n, void *out)
 {
@@ -2013,20 +2031,27 @@ spk_status spk_deliver_noalloc(spk_net *net, const uint32_t *d_spikes, uint64_t 
     hipError_t e = hipSuccess;
     bool capturing = false;
     uint32_t *zero_area = nullptr;  // binned delivery: the scratch's
-    if (!net->direct) {
+    bool binned = !net->direct;
+    if (binned_pays(net, n_spikes, delay)) {
+        binned = true;
+        a.direct = 0;
+        a.pg1 = push_blocks_per_group();
+    }
+    if (binned) {
         // Carve the zero area: fill counters, overflow flags and overflow
         // accumulators of one arrival slot; pages of as many records as the
         // bytes they leave of one area's size hold (at most the debug
         // capacity; events beyond it take the overflow accumulators, with the
         // same sums)
         auto up = [](uint64_t b) { return (b + 255) / 256 * 256; };
-        const uint64_t n_pages = (uint64_t)kGroups * net->pg1 * tl.T8;
+        const uint64_t n_pages = (uint64_t)kGroups * a.pg1 * tl.T8;
         const uint64_t acc_bytes = (uint64_t)tl.T * tl.W * (net->P.acc_mode == SPK_ACC_FIXED ? 4 : 8);
         const uint64_t o_fill = 0, o_flag = up(n_pages * 4), o_acc = o_flag + up((uint64_t)tl.T * 4);
         const uint64_t used = o_acc + up(acc_bytes);
         const uint64_t rec = net->compact ? 2 : 8;
         const uint64_t room = used < kNoAllocScratchBytes ? kNoAllocScratchBytes - used : 0;
-        uint64_t cap = std::min<uint64_t>(room / (n_pages * rec), std::min<uint64_t>(kDebugPageCap, net->page_cap));
+        uint64_t cap = std::min<uint64_t>(room / (n_pages * rec), kDebugPageCap);
+        if (!net->direct) cap = std::min<uint64_t>(cap, net->page_cap);
         cap = cap / 16 * 16;
         if (cap < 16)
             return fail(SPK_EOVERFLOW, "network too large for the fixed scratch of spk_deliver_noalloc (" +

@@ -74,7 +74,9 @@ struct PushLDS {
 // Dependent memory round trips: spike counts, spike IDs, row descriptors,
 // synapses; the page writes are not waited for.  Compact synapses (CMP) give
 // 2-byte page records class << 13 | local.
-template <bool FIXED, bool CMP>
+// TOFF: rows of a network of direct delivery, found by their tile offsets
+// instead of a descriptor (deliveries of a given spike list only).
+template <bool FIXED, bool CMP, bool TOFF>
 __global__ __launch_bounds__(kPushThreads) void k_push(StepArgs a, uint32_t i, int64_t t_explicit)
 {
     using Rec = typename SynRec<CMP>::T;
@@ -113,11 +115,17 @@ __global__ __launch_bounds__(kPushThreads) void k_push(StepArgs a, uint32_t i, i
             const bool bad = s >= a.n;
             if (bad && x == 0) atomicOr(a.flags, kFlagBadSpike);
             s = bad ? 0u : s;
-            const RowDesc *d = a.desc + s;
-            const uint32_t lo = x ? d->gend[x - 1] : 0u, hi = d->gend[x];
-            len = bad ? 0u : hi - lo;
-            base = d->start + lo;
-            emitted += bad ? 0u : d->gend[kGroups - 1];
+            if constexpr (TOFF) {
+                const uint16_t *to = a.toff + (uint64_t)s * (tl.T + 1) + x * tl.T8;
+                len = bad ? 0u : (uint32_t)to[tl.T8] - to[0];
+                base = a.row_ptr[s] + to[0];
+            } else {
+                const RowDesc *d = a.desc + s;
+                const uint32_t lo = x ? d->gend[x - 1] : 0u, hi = d->gend[x];
+                len = bad ? 0u : hi - lo;
+                base = d->start + lo;
+                emitted += bad ? 0u : d->gend[kGroups - 1];
+            }
         }
         // rows are cut into chunks of 64 events; wave w takes chunks w, w + nw,
         // ...: lane l reads event l of the chunk (one uniform lookup per chunk)
@@ -628,12 +636,16 @@ hipError_t launch_push(const StepArgs &a, uint32_t i, int64_t t_explicit, hipStr
         return hipErrorInvalidValue;
     if (a.compact ? (!a.syn32 || !a.pages16) : (!a.syn || !a.pages)) return hipErrorInvalidValue;
     const dim3 grid(kGroups * a.pg1), block(kPushThreads);
-    if (a.compact) {
-        if (a.m.fixed) hipLaunchKernelGGL((k_push<true, true>), grid, block, 0, s, a, i, t_explicit);
-        else hipLaunchKernelGGL((k_push<false, true>), grid, block, 0, s, a, i, t_explicit);
+    if (!a.desc) {
+        if (!a.toff || !a.compact || !a.dbg_spikes) return hipErrorInvalidValue;
+        if (a.m.fixed) hipLaunchKernelGGL((k_push<true, true, true>), grid, block, 0, s, a, i, t_explicit);
+        else hipLaunchKernelGGL((k_push<false, true, true>), grid, block, 0, s, a, i, t_explicit);
+    } else if (a.compact) {
+        if (a.m.fixed) hipLaunchKernelGGL((k_push<true, true, false>), grid, block, 0, s, a, i, t_explicit);
+        else hipLaunchKernelGGL((k_push<false, true, false>), grid, block, 0, s, a, i, t_explicit);
     } else {
-        if (a.m.fixed) hipLaunchKernelGGL((k_push<true, false>), grid, block, 0, s, a, i, t_explicit);
-        else hipLaunchKernelGGL((k_push<false, false>), grid, block, 0, s, a, i, t_explicit);
+        if (a.m.fixed) hipLaunchKernelGGL((k_push<true, false, false>), grid, block, 0, s, a, i, t_explicit);
+        else hipLaunchKernelGGL((k_push<false, false, false>), grid, block, 0, s, a, i, t_explicit);
     }
     return hipGetLastError();
 }

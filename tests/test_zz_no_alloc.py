@@ -78,6 +78,43 @@ def test_noalloc_equals_debug_deliver(env, name, mk, delays):
     g.close()
 
 
+RESIDENT = [  # parameters, spikes: lists that resident networks deliver by tile, and longer ones through pages
+    (lambda: I.scaled(4, 20_000, k_out=1500), (300, 4000)),
+    (lambda: I.scaled(2, 6000, k_in_exc=800, k_in_inh=200), (50, 4000)),
+    (lambda: I.config(0, n=4000, p=0.25, delay_max=3), (50, 2000)),
+    (lambda: I.config(0, n=1000, p=0.5), (10, 1000, 20_000)),  # (the last: IDs repeated, pages overflow)
+    (lambda: I.scaled(4, 131_072, k_out=100, delay_max=4), (1000, 131_072)),
+]
+
+
+@pytest.mark.parametrize("mk,counts", RESIDENT, ids=[str(k) for k in range(len(RESIDENT))])
+@pytest.mark.parametrize("acc", [I.ACC_F32, I.ACC_FIXED], ids=["f32", "fixed"])
+def test_noalloc_on_resident_networks(env, mk, counts, acc):
+    torch, spk = env
+    cfg = dict(mk(), acc_mode=acc)
+    g = spk.Net(cfg, max_steps=1)
+    n = cfg["n"]
+    assert g.stats()["page_cap"] == 0
+    for count in counts + counts[:1]:
+        spikes = I.spike_set(n, count, seed=count, unique=count <= n)
+        for delay in sorted({0, cfg["delay_min"], cfg["delay_max"]}):
+            got = _noalloc(torch, g, spikes, delay, acc == I.ACC_FIXED)
+            want = g.debug_deliver(spikes, delay=delay)
+            assert np.array_equal(got.view(np.uint32), want.view(np.uint32)), (count, delay)
+    # an ID out of range in a long list
+    ids = np.append(spikes.repeat(-(-counts[-1] // len(spikes))), np.uint32(n)).astype(np.int32)
+    out = torch.zeros(n, dtype=torch.int32 if acc else torch.float32, device="cuda")
+    d = torch.from_numpy(ids).cuda()
+    torch.cuda.synchronize()
+    g.deliver_noalloc(d.data_ptr(), len(ids), out.data_ptr())
+    with pytest.raises(spk.SpkError) as e:
+        g.sync()
+    assert e.value.code == spk.SPK_EINVAL
+    want = g.debug_deliver(ids[:-1].astype(np.uint32))
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32))
+    g.close()
+
+
 def test_noalloc_full_size_network(env):
     # 2,000,000 neurons in 248 tiles of 8,192: the scratch holds the overflow
     # accumulators (16 MiB) and pages of 976 records; 20,000 spikes (3e7
