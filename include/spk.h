@@ -136,6 +136,9 @@ enum { SPK_STEP_AUTO = 0, SPK_STEP_GRAPH = 1, SPK_STEP_PERSISTENT = 2 };
  *   page of binned delivery (default: an equal share of 2 GiB);
  *   SPK_BATCH_STEPS caps the
  *   steps per batch (1..16, default 8; spk_stats_t.batch_steps);
+ *   SPK_GEN_KEYS=0 makes the Bernoulli generator draw every row a second
+ *   time to place it instead of keeping the first pass's synapses, 1 keeps
+ *   them in small networks too (the results are the same);
  *   SPK_RING=0 leaves out the steps with every pending input in LDS
  *   (spk_params.step_mode) and their tiling, SPK_RING=64 .. 8192 (a power of
  *   two) sets the neurons per tile there (the results are the same). */

@@ -369,10 +369,12 @@ struct RingArgs {
 
 // spk_gen.hip -- connectivity expansion
 // hist: optional (Bernoulli rows), n * (T + 2 * kGroups) u16 bucket counts
-// kept for gen_fill_rows, which then need not count the rows again.
-hipError_t gen_count_rows(const ConnArgs &c, uint32_t *cnt, uint16_t *hist, hipStream_t s);
+// kept for gen_fill_rows, which then need not count the rows again; keys:
+// optional with hist, n * cap synapses kept likewise (the first cap of a row).
+hipError_t gen_count_rows(const ConnArgs &c, uint32_t *cnt, uint16_t *hist, uint32_t *keys, uint32_t cap,
+                          hipStream_t s);
 hipError_t gen_fill_rows(const ConnArgs &c, const uint64_t *row_ptr, void *syn, RowIndex ix,
-                         const uint16_t *hist, hipStream_t s);
+                         const uint16_t *hist, const uint32_t *keys, uint32_t cap, hipStream_t s);
 // Bernoulli rows grouped by tile, drawn once, for expected rows well below
 // kBernStage: syn has room synapses; *cursor (zero on entry) ends as their
 // number, or beyond room where the rows did not fit.

@@ -114,20 +114,31 @@ GEN_CASES = [
 FORMATS = [(1, "full"), (0, "auto")]
 
 
+def _two_pass_rows(spk, cfg):
+    """Bernoulli rows of a network that is not drawn in one pass (graph path
+    or binned delivery), against the oracle's."""
+    for over in (dict(step_mode=1), dict(delivery=2)):
+        g = spk.Net(dict(cfg, **over), max_steps=1)
+        st = g.stats()
+        assert st["step_mode"] == 1 or st["page_cap"] > 0
+        o = oracle.Net(cfg)
+        o_rp, o_col, o_w, o_d = o.csr()
+        assert st["nnz"] == len(o_col)
+        offs, col, w, d = g.csr()
+        _compare_rows(offs, col, w, d, o_rp, o_col, o_w, o_d, range(cfg["n"]), cfg["acc_mode"] == I.ACC_FIXED)
+
+
+@pytest.mark.parametrize("keys", ["0", "1"], ids=["drawn-again", "kept"])
 @pytest.mark.parametrize("name", ["C0", "C1-3000", "bern-delays"])
-def test_generator_two_draws_equals_oracle(spk, name, monkeypatch):
+def test_generator_two_draws_equals_oracle(spk, name, keys, monkeypatch):
     """Bernoulli rows placed by drawing every row a second time (the path
-    taken where a row is longer than the first pass can keep) equal the
-    oracle's rows too."""
-    monkeypatch.setenv("SPK_GEN_KEYS", "0")
+    taken in small networks and where a row is longer than the first pass can
+    keep), and from the synapses that the first pass kept, equal the
+    oracle's rows."""
+    monkeypatch.setenv("SPK_GEN_KEYS", keys)
     cfg = dict(GEN_CASES)[name]()
     _say(f"[gen two draws] {name} n={cfg['n']}")
-    g = spk.Net(cfg, max_steps=1)
-    o = oracle.Net(cfg)
-    o_rp, o_col, o_w, o_d = o.csr()
-    assert g.stats()["nnz"] == len(o_col)
-    offs, col, w, d = g.csr()
-    _compare_rows(offs, col, w, d, o_rp, o_col, o_w, o_d, range(cfg["n"]), cfg["acc_mode"] == I.ACC_FIXED)
+    _two_pass_rows(spk, cfg)
 
 
 def test_generator_without_count_keeping_equals_oracle(spk, monkeypatch):
@@ -135,12 +146,7 @@ def test_generator_without_count_keeping_equals_oracle(spk, monkeypatch):
     (the path taken where they cannot be allocated: SPK_GEN_HIST=0) equal the
     oracle's rows."""
     monkeypatch.setenv("SPK_GEN_HIST", "0")
-    cfg = I.config(0, n=1500, p=0.05, delay_min=2, delay_max=9, seed=4)
-    g = spk.Net(cfg, max_steps=1)
-    o = oracle.Net(cfg)
-    o_rp, o_col, o_w, o_d = o.csr()
-    offs, col, w, d = g.csr()
-    _compare_rows(offs, col, w, d, o_rp, o_col, o_w, o_d, range(cfg["n"]), False)
+    _two_pass_rows(spk, I.config(0, n=1500, p=0.05, delay_min=2, delay_max=9, seed=4))
 
 
 @pytest.mark.parametrize("atomics", ["0", "1"], ids=["lds", "per-synapse"])
