@@ -112,16 +112,19 @@ def test_full_size_bench_configuration_sampled(spk_full, step_mode):
     _say("[full] sampled update ok")
 
 
-def test_full_size_delay15_batch_sampled(spk_full):
+@pytest.mark.parametrize("ring", [None, "0"], ids=["resident", "pages"])
+def test_full_size_delay15_batch_sampled(spk_full, ring, monkeypatch):
     """The 1e9-synapse network with delay 15 (100,000 LIF, in-degree 8,000
     excitatory + 2,000 inhibitory, Poisson drive, fp32 accumulation) in the
-    configuration bench.py --config 2 times: the persistent kernel in batches
-    of 8 steps.  After 300 steps, one more batch; for sampled
+    configuration bench.py --config 2 times, the resident kernel in batches of
+    8 steps, and in the page kernel (SPK_RING=0).  After 300 steps, one more batch; for sampled
     neurons the oracle draws the in-synapses (its per-target generator), sums
     the weights of those whose source fired 15 steps earlier exactly, and
     runs its single-neuron update for each step: every spike decision of the batch
     and the final state must equal the library's bit for bit."""
     spk = spk_full
+    if ring:
+        monkeypatch.setenv("SPK_RING", ring)
     cfg = I.config(2, driven=True)
     n, D, d = cfg["n"], 8, cfg["delay_min"]
     T0 = 300
@@ -130,6 +133,7 @@ def test_full_size_delay15_batch_sampled(spk_full):
     st = g.stats()
     assert st["step_mode"] == spk.SPK_STEP_PERSISTENT
     assert st["delivery"] == spk.SPK_DELIVERY_BINNED and st["batch_steps"] == D
+    assert (st["page_cap"] > 0) == (ring == "0")
     assert st["nnz"] == n * (cfg["k_in_exc"] + cfg["k_in_inh"])
     s64 = int(st["fixed_shift"])
     g.step(T0)

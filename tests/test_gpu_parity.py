@@ -314,11 +314,22 @@ RUN_CASES = [
 # persistent kernel with batches capped at 1, 4 and 16 steps (SPK_BATCH_STEPS)
 MODES = [("graph", 1, False, None), ("launch", 1, True, None), ("persist", 2, False, None),
          ("persist-prof", 2, True, None), ("persist-batch1", 2, False, "1"),
-         ("persist-batch4", 2, False, "4"), ("persist-batch16", 2, False, "16")]
+         ("persist-batch4", 2, False, "4"), ("persist-batch16", 2, False, "16"),
+         # direct delivery in the persistent kernel that reads the due rows,
+         # which the resident kernel else stands in for (SPK_RING=0)
+         ("persist-rows", 2, False, None)]
 
 
 def _expected_batch(cfg, batch):
     return min(cfg["delay_min"], int(batch) if batch else 8)
+
+
+def _general_tile_width(n):
+    """Neurons per tile outside the resident kernel (up to 256 tiles, at least 64 neurons)."""
+    w = 64
+    while -(-n // (8 * w)) > 32:
+        w *= 2
+    return w
 
 
 def _persistent_applies(cfg, delivery):
@@ -346,10 +357,16 @@ def test_fixed_point_simulation_bit_identical(spk, name, mk, T, delivery, mode, 
         pytest.skip("steps are batched only with binned delivery and a smallest delay >= 2")
     if batch:
         monkeypatch.setenv("SPK_BATCH_STEPS", batch)
+    if mode == "persist-rows":
+        if delivery == 2:
+            pytest.skip("binned delivery does not take the resident kernel")
+        monkeypatch.setenv("SPK_RING", "0")
     _say(f"[run] {name} n={cfg['n']} T={T} delivery={delivery} mode={mode} format={fmt}")
     g = spk.Net(cfg, max_steps=T, raster_capacity=cfg["n"] * T)
     st = g.stats()
     assert st["step_mode"] == step_mode
+    if mode == "persist-rows":
+        assert st["tile_width"] == _general_tile_width(cfg["n"])
     persist_binned = step_mode == 2 and delivery == 2
     assert st["batch_steps"] == (_expected_batch(cfg, batch) if persist_binned else 1)
     g.set_profiling(profiled)
@@ -438,9 +455,13 @@ DEGENERATE = [
 
 @pytest.mark.parametrize("name,mk,T", DEGENERATE, ids=[c[0] for c in DEGENERATE])
 @pytest.mark.parametrize("delivery", [1, 2], ids=["direct", "binned"])
-@pytest.mark.parametrize("step_mode", [1, 2], ids=["graph", "persist"])
-def test_degenerate_networks_bit_identical(spk, name, mk, T, delivery, step_mode):
+@pytest.mark.parametrize("step_mode,ring", [(1, None), (2, None), (2, "0")], ids=["graph", "persist", "persist-rows"])
+def test_degenerate_networks_bit_identical(spk, name, mk, T, delivery, step_mode, ring, monkeypatch):
     cfg = mk()
+    if ring:
+        if delivery == 2:
+            pytest.skip("binned delivery does not take the resident kernel")
+        monkeypatch.setenv("SPK_RING", ring)
     cfg["acc_mode"] = I.ACC_FIXED
     cfg["delivery"] = delivery
     cfg["step_mode"] = step_mode
@@ -469,15 +490,20 @@ RANDOM_SEEDS = list(range(1, 25))
 
 
 @pytest.mark.parametrize("seed", RANDOM_SEEDS)
-def test_random_shapes_bit_identical(spk, seed):
+def test_random_shapes_bit_identical(spk, seed, monkeypatch):
     base = I.random_shape(seed)
     base["acc_mode"] = I.ACC_FIXED
     base["syn_format"] = FORMATS[seed % len(FORMATS)][0]
     T = 150
     r, ov, orf, _ = _oracle_run(base, T)
     assert r["counts"].sum() > 0
-    runs = [(2, 1), (2, 2)] + ([(1, 1), (1, 2)] if base["delay_min"] == base["delay_max"] else [])
-    for delivery, step_mode in runs:
+    # (delivery, step mode, SPK_RING): pages, the due rows, and AUTO (the resident kernel)
+    runs = [(2, 1, None), (2, 2, None), (0, 2, None)]
+    if base["delay_min"] == base["delay_max"]:
+        runs += [(1, 1, None), (1, 2, None), (1, 2, "0")]
+    for delivery, step_mode, ring in runs:
+        if ring:
+            monkeypatch.setenv("SPK_RING", ring)
         cfg = dict(base, delivery=delivery, step_mode=step_mode)
         _say(f"[random] seed={seed} n={cfg['n']} kind={cfg['conn_kind']} delays={cfg['delay_min']}-"
              f"{cfg['delay_max']} format={cfg['syn_format']} delivery={delivery} step_mode={step_mode}")
@@ -604,13 +630,16 @@ def test_bin_overflow_fallback(spk, acc, fmt, step_mode, delays, monkeypatch):
 
 
 @pytest.mark.parametrize("delays", [(1, 20), (3, 9), (15, 15)], ids=["d1-20", "d3-9", "d15"])
-@pytest.mark.parametrize("step_mode", [1, 2], ids=["graph", "persist"])
-def test_resume_matches_single_run(spk, step_mode, delays):
+@pytest.mark.parametrize("step_mode,ring", [(1, None), (2, None), (2, "0")], ids=["graph", "resident", "pages"])
+def test_resume_matches_single_run(spk, step_mode, ring, delays, monkeypatch):
     # calls of 50 and 70 steps, and of one step each: batches of several steps
     # (smallest delay 3 or 15) end early at the end of a call
     cfg = I.scaled(4, 5000, k_out=500, acc_mode=I.ACC_FIXED, step_mode=step_mode,
                    delay_min=delays[0], delay_max=delays[1])
+    if ring:
+        monkeypatch.setenv("SPK_RING", ring)
     a = spk.Net(cfg, max_steps=120, raster_capacity=5000 * 120)
+    assert (a.stats()["page_cap"] == 0) == (delays[0] == delays[1] if step_mode == 1 else not ring)
     b = spk.Net(cfg, max_steps=120, raster_capacity=5000 * 120)
     a.step(50)
     a.step(70)
@@ -627,8 +656,10 @@ def test_resume_matches_single_run(spk, step_mode, delays):
     assert np.array_equal(a.delivered(), b.delivered())
 
 
-@pytest.mark.parametrize("step_mode", [1, 2], ids=["graph", "persist"])
-def test_delay_chain_spike_timing(spk, step_mode):
+@pytest.mark.parametrize("step_mode,ring", [(1, None), (2, None), (2, "0")], ids=["graph", "resident", "pages"])
+def test_delay_chain_spike_timing(spk, step_mode, ring, monkeypatch):
+    if ring:
+        monkeypatch.setenv("SPK_RING", ring)
     delays = [1, 3, 2, 5]
     n = 5
     row_ptr = np.array([0, 1, 2, 3, 4, 4], dtype=np.uint64)
@@ -858,9 +889,14 @@ def test_persistent_equals_graph_fp32(spk, name, mk, T, fmt, delivery, monkeypat
     cfg["syn_format"] = fmt
     cfg["delivery"] = delivery
     runs = []
-    for step_mode, batch in ((1, None), (2, None), (2, "1")):
+    for step_mode, batch, ring in ((1, None, None), (2, None, None), (2, "1", None), (2, None, "0")):
         if batch:
             monkeypatch.setenv("SPK_BATCH_STEPS", batch)
+        if ring:  # AUTO: pages or the due rows instead of the resident kernel
+            if delivery == 2:
+                continue
+            monkeypatch.delenv("SPK_BATCH_STEPS")
+            monkeypatch.setenv("SPK_RING", ring)
         c = dict(cfg, step_mode=step_mode)
         g = spk.Net(c, max_steps=T, raster_capacity=cfg["n"] * T)
         st = g.stats()

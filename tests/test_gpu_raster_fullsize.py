@@ -12,7 +12,8 @@ sizes and in the launch configuration bench.py times:
     overflow path delivers part of every step's events;
   - the 1e9-synapse source network (1,000,000 Bernoulli sources, fan-out
     1,000, w ~ U[0, 1e-3)) at 10 Hz for 100 steps and at 50 Hz for 20 steps,
-    direct delivery, tiles of 4,096 neurons;
+    direct delivery, tiles of 4,096 neurons, in the resident kernel and at
+    10 Hz in the one that reads the due rows;
   - both networks with procedural synapses (none stored: every fired row is
     generated again from the hash; binned delivery, steps as graphs).
 
@@ -192,10 +193,14 @@ def test_c4_fixed_point_100_steps_bit_identical(spk_mod, page_cap, fmt, monkeypa
 
 
 @pytest.mark.timeout(900)
-@pytest.mark.parametrize("key,fmt", [(_C3_10, 0), (_C3_50, 0), (_C3_10, 3)],
-                         ids=["c3-10hz", "c3-50hz", "c3-10hz-procedural"])
-def test_c3_sources_fixed_point_bit_identical(spk_mod, key, fmt):
+@pytest.mark.parametrize("key,fmt,ring", [(_C3_10, 0, None), (_C3_50, 0, None), (_C3_10, 3, None), (_C3_10, 0, "0")],
+                         ids=["c3-10hz", "c3-50hz", "c3-10hz-procedural", "c3-10hz-due-rows"])
+def test_c3_sources_fixed_point_bit_identical(spk_mod, key, fmt, ring, monkeypatch):
+    # the resident kernel, and (SPK_RING=0) the persistent kernel that reads
+    # the due rows
     spk = spk_mod
+    if ring:
+        monkeypatch.setenv("SPK_RING", ring)
     start_oracle_jobs([key])
     cfg = dict(_cfg(key[0]), syn_format=fmt)
     _say(f"[raster] {key[0]} n={cfg['n']} T={key[1]} format={fmt}")
@@ -215,16 +220,19 @@ def test_c3_sources_fixed_point_bit_identical(spk_mod, key, fmt):
     _say(f"[raster] {key[0]} identical")
 
 
-def test_c1_bernoulli_sampled_inputs(spk_mod):
+@pytest.mark.parametrize("ring", [None, "0"], ids=["resident", "due-rows"])
+def test_c1_bernoulli_sampled_inputs(spk_mod, ring, monkeypatch):
     """The 250,000-neuron Bernoulli network (p = 0.02, 1.25e9 synapses, delay
     1, Poisson drive) as bench.py --config 1 times it (fp32 accumulation,
-    persistent kernel, direct delivery, tiles of 1,024): after 200 steps, one
+    resident kernel, direct delivery, tiles of 1,024): after 200 steps, one
     more step; the input of 256 sampled neurons is the sum over the spikes
     of the previous step of the weights of the connected pairs (the
     oracle's pair predicate), summed exactly here and rounded once as the
     library does, and the oracle's single-neuron update with that input must
     reproduce the library's V, refractory counter and spike decision."""
     spk = spk_mod
+    if ring:  # (the persistent kernel that reads the due rows)
+        monkeypatch.setenv("SPK_RING", ring)
     cfg = I.config(1, driven=True)
     n, T0 = cfg["n"], 200
     _say(f"[raster] c1 sampled n={n}")
