@@ -360,7 +360,7 @@ def main():
             "steps": "one persistent launch" if persistent else "HIP graphs of 32 steps",
             "batch_steps": st["batch_steps"],
             "synapse_bytes": bpe,
-            "accumulation": "exact int64 fixed point, rounded once to fp32" if args.acc == "f32"
+            "accumulation": "exact integer sums, rounded once to fp32" if args.acc == "f32"
                             else f"int32 fixed point 2^-{cfg['fixed_shift']}",
             "settle_steps": S,
             "mean_rate_hz": round(rate_hz, 3),

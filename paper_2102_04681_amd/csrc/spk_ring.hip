@@ -101,19 +101,20 @@ __device__ __forceinline__ bool box_ready(Box x, uint32_t e)
     return ((uint32_t)x.a & 0x3ffffu) == (e & 0x3ffffu) && (c < 2 || c > kInline || ((uint32_t)x.b & 0xffu) == (e & 0xffu));
 }
 
-__device__ __forceinline__ uint64_t ld_ag64(const uint64_t *p)
-{
-    return __hip_atomic_load(const_cast<uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ void st_ag64(uint64_t *p, uint64_t v)
 {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Both words of mailbox k in one 16-byte load at agent scope (sc1; volatile:
-// polled in loops).  The load need not be atomic: each word is checked on its
-// own.  One request per mailbox and look instead of two took 250,000 neurons
-// from 9.5 to 9.3 us per step, four instead of two had cost 1.7: the looks of
-// every workgroup queue.
+// polled in loops).  The two words may be of different stores: each is
+// checked on its own.  The halves of one 8-byte word have to be of one store,
+// which rests on the hardware and not on the language's memory model: an
+// aligned 8-byte store and an aligned 16-byte load of a lane are each one
+// access within a 128-byte line.  (A stamp in each 4-byte word, which needs no
+// such thing, took 250,000 neurons from 8.8 to 9.9 us per step.)  One request
+// per mailbox and look instead of two took 250,000 neurons from 9.5 to 9.3
+// us per step, four instead of two had cost 1.7: the looks of every workgroup
+// queue.
 __device__ __forceinline__ Box box_load(const uint64_t *boxes, uint32_t k)
 {
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)boxes, 0, kRingBoxBytes, 0x00027000);

@@ -661,7 +661,11 @@ void plan_ring(spk_net *net, uint64_t nnz_expected, const uint64_t *in_max)
     //   of 64, 7.2 / 18.8 / 44 on 5 of 512, 9.9 / 10.5 / 19.8 in the page
     //   kernel); more mailboxes to poll cost more than that gives at ordinary
     //   rates (4,000 neurons 3.8 on 32 tiles, 4.0 on 63; 30,000 4.8 on 59
-    //   tiles of 512, 5.2 on 118, 6.6 on 235);
+    //   tiles of 512, 5.2 on 118, 6.6 on 235), and fewer do where tiles twice
+    //   as wide would have few events in a step (300 of sources: 2,500 at 2 Hz
+    //   3.6 on 20 tiles, 3.7 on 10, 4.4 on 5 with 820 each; 1,000 of neurons at
+    //   their most, a tenth of that as a rule: 4,852 neurons with fan-out 68
+    //   4.1 on 10 tiles, 4.3 on 38), batches apart;
     //   from 512 on at most 128 tiles (120,000 neurons: 6.2 on 118 tiles of
     //   1,024, 7.0 on 235 of 512), but not wider than 2,048 for it (300,000:
     //   7.9 on 147 tiles of 2,048, 8.6 on 74 of 4,096);
@@ -693,7 +697,8 @@ void plan_ring(spk_net *net, uint64_t nnz_expected, const uint64_t *in_max)
         W = W1;
     } else {
         const uint32_t most = nnz >= 400000000ull ? kRingMaxT : 128;
-        for (W = 64; W < 512 && tiles(W) > 48; W <<= 1) {}
+        const double few = batches ? 0.0 : source ? 300.0 : 1000.0;
+        for (W = 64; W < 512 && (tiles(W) > 48 || ev <= few * tiles(2 * W)); W <<= 1) {}
         for (; W < kMaxTileW; W <<= 1)
             if (tiles(W) <= most || (W >= 2048 && tiles(W) <= kRingMaxT)) break;
         while (W > 64 && ev > 8000.0 * tiles(W) && tiles(W >> 1) <= (source ? kRingMaxT : 80u)) W >>= 1;

@@ -102,8 +102,11 @@ WIDTHS = [  # parameters, neurons per tile of the resident kernel
     (lambda: I.scaled(4, 1000, k_out=100, delay_min=2, delay_max=4), 64),    # (batches)
     (lambda: I.scaled(3, 1000, k_out=300, rate_hz=10.0), 1024), (lambda: I.scaled(3, 1000, k_out=300, rate_hz=50.0), 64),
     (lambda: I.scaled(3, 2000, k_out=300, rate_hz=3.0), 2048), (lambda: I.scaled(3, 2000, k_out=300, rate_hz=10.0), 64),
-    (lambda: I.scaled(4, 3072, k_out=50, delay_max=4), 64), (lambda: I.scaled(4, 3073, k_out=50, delay_max=4), 128),
-    (lambda: I.scaled(4, 12288, k_out=50, delay_max=4), 256), (lambda: I.scaled(4, 12289, k_out=50, delay_max=4), 512),
+    (lambda: I.scaled(4, 3072, k_out=700, delay_max=4), 64), (lambda: I.scaled(4, 3073, k_out=700, delay_max=4), 128),
+    (lambda: I.scaled(4, 12288, k_out=700, delay_max=4), 256), (lambda: I.scaled(4, 12289, k_out=700, delay_max=4), 512),
+    (lambda: I.scaled(4, 4852, k_out=68, delay_max=4), 512),  # (few events)
+    (lambda: I.scaled(4, 4852, k_out=68, delay_min=2, delay_max=4), 128),
+    (lambda: I.scaled(3, 2500, k_out=400, rate_hz=2.0), 256),
     (lambda: I.scaled(4, 12289, k_out=1000, delay_max=4, t_ref_ms=0.0), 256),
     (lambda: I.scaled(4, 65536, k_out=50, delay_max=4), 512), (lambda: I.scaled(4, 65537, k_out=50, delay_max=4), 1024),
     # rows grouped by narrower tiles, and by the same where the narrower ones' offsets take more than 64 MB
