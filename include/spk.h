@@ -83,8 +83,8 @@ enum { SPK_FORMAT_AUTO = 0, SPK_FORMAT_FULL = 1, SPK_FORMAT_COMPACT = 2, SPK_FOR
  * the network's seed and parameters when its events are filed, the same
  * synapses the other formats store.  Generated fixed out-degree networks
  * only; binned delivery, steps run as graphs (SPK_EINVAL otherwise); each
- * fired row costs one hash per synapse in each of the 8 XCD groups instead
- * of 4 or 8 bytes per synapse read.  spk_stats_t.bytes_per_synapse is 0. */
+ * fired row costs two or three hashes per synapse instead of 4 or 8 bytes
+ * per synapse read.  spk_stats_t.bytes_per_synapse is 0. */
 /* How spk_step runs the steps (same results, different speed).  GRAPH: each
  * step is a tile kernel (+ push kernel for binned delivery), batches of steps
  * replayed from captured HIP graphs.  PERSISTENT: all steps of one spk_step
@@ -177,10 +177,11 @@ typedef struct {
     int32_t fixed_shift;       /* fixed mode: S; fp32 mode: the unit 2^-S64 of the exact sums */
     float k;
     double bytes_per_synapse;  /* synapse storage / nnz: 8 (FULL), 4 (COMPACT), 0 (PROCEDURAL) */
-    uint32_t tile_width;       /* target neurons per tile (one workgroup each) */
+    uint32_t tile_width;       /* target neurons per tile of the steps (one workgroup each) */
     uint32_t tiles;
     uint32_t delivery;         /* SPK_DELIVERY_DIRECT or SPK_DELIVERY_BINNED as chosen */
-    uint32_t page_cap;         /* binned delivery: records per page (beyond: global atomics) */
+    uint32_t page_cap;         /* binned delivery: records per page (beyond: global atomics);
+                                  0 where no pages are kept (direct delivery, pending inputs in LDS) */
     uint32_t step_mode;        /* SPK_STEP_GRAPH or SPK_STEP_PERSISTENT as chosen */
     uint32_t batch_steps;      /* persistent kernel, binned delivery: steps run as
                                   one batch (tile phases back to back, then one filing pass);
@@ -298,7 +299,7 @@ spk_status spk_debug_deliver(spk_net *net, const uint32_t *spikes, uint64_t n_sp
  * memset and does not synchronise.  Every call on one device shares them:
  * calls that overlap on one device (any network, any stream, replays of
  * captured calls among them) race, so the caller orders them (one stream, or
- * events).  Direct delivery needs no
+ * events).  Networks of direct delivery (spk_stats_t.delivery) need no
  * scratch.  Results equal spk_debug_deliver's.  Network state is not
  * changed.  Errors (returned at once): SPK_EINVAL (null output, bad delay,
  * n_spikes >= 2^30), SPK_EOVERFLOW (the network's tiles need more overflow

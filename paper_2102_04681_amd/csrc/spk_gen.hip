@@ -2,10 +2,11 @@
 // network description is expanded on the device, not uploaded synapse by
 // synapse) for gfx950 (MI355X, wave64).
 //
-// Layout produced: one row per source neuron at [row_ptr[s], row_ptr[s+1]),
-// synapse = int2 {j << 24 | target, weight bits} (full format) or u32
-// {class << 30 | j << 24 | target} (compact format: at most four distinct
-// weights, looked up by class), j = delay - delay_min.
+// Layout produced: one row per source neuron from row_ptr[s] on, outdeg[s]
+// long (rows follow each other by source, but for Bernoulli rows drawn once,
+// which lie in no order), synapse = int2 {j << 24 | target, weight bits}
+// (full format) or u32 {class << 30 | j << 24 | target} (compact format: at
+// most four distinct weights, looked up by class), j = delay - delay_min.
 // Every row is grouped by target range (the paper keeps rows sorted by target,
 // Sec. III-A, so that each target range of a row is one contiguous run; only
 // the grouping matters for delivery, the order inside a range does not).

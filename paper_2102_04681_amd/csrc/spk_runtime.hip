@@ -669,9 +669,12 @@ void plan_ring(spk_net *net, uint64_t nnz_expected, const uint64_t *in_max)
     //   from 512 on at most 128 tiles (120,000 neurons: 6.2 on 118 tiles of
     //   1,024, 7.0 on 235 of 512), but not wider than 2,048 for it (300,000:
     //   7.9 on 147 tiles of 2,048, 8.6 on 74 of 4,096);
-    //   from 4e8 synapses on the gather decides, on as many compute units as
-    //   there are (250,000 neurons, 1.25e9 synapses: 8.8 on 245 tiles, 10.0
-    //   on 123; delay 15 and 1e9 synapses: 2.0 on 196, 2.6 on 98).
+    //   from 7e8 synapses on the gather decides, on as many compute units as
+    //   there are (120,000 neurons on 235 / 118 tiles: 4e8 synapses 6.4 / 5.9,
+    //   7e8 6.8 / 6.9; 250,000 on 245 / 123: 4e8 7.3 / 6.7, 7e8 7.7 / 7.3,
+    //   1.25e9 8.8 / 10.0), in batches, whose polling is shared, from 4e8 on
+    //   (delay 15: 120,000 neurons, 4e8 1.9 / 2.4; 100,000, 1e9 2.0 on 196, 2.6
+    //   on 98).
     //   Where a tile would deliver more than 8,000 events per step, narrower
     //   ones (sources, 5,100 per tile: 60,000 at 10 Hz 7.7 on 118 tiles, 9.0
     //   on 235; 12,700: 20,000 at 50 Hz 10.0 on 79, 8.6 on 157); neurons, which
@@ -696,7 +699,7 @@ void plan_ring(spk_net *net, uint64_t nnz_expected, const uint64_t *in_max)
     } else if (net->n <= 2048 && !batches && ev <= ev1 && fits(W1)) {
         W = W1;
     } else {
-        const uint32_t most = nnz >= 400000000ull ? kRingMaxT : 128;
+        const uint32_t most = nnz >= (batches ? 400000000ull : 700000000ull) ? kRingMaxT : 128;
         const double few = batches ? 0.0 : source ? 300.0 : 1000.0;
         for (W = 64; W < 512 && (tiles(W) > 48 || ev <= few * tiles(2 * W)); W <<= 1) {}
         for (; W < kMaxTileW; W <<= 1)
@@ -1591,16 +1594,27 @@ void destroy_net(spk_net *net)
     delete net;
 }
 
+// Whether the resident kernel's network counts as binned: its events are
+// filed by arrival step right after their spike, as binned delivery does; with
+// one delay of one step, or where direct delivery was asked for, a tile reads
+// the due rows.
+bool ring_binned(const spk_net *net)
+{
+    return net->ring && net->P.delivery != SPK_DELIVERY_DIRECT && net->dmax > 1;
+}
+
 // Whether a given spike list is delivered faster through pages than by each
 // tile reading its runs, on a resident network's rows.  Microseconds of
 // spk_deliver_noalloc, E = 1e6 events, T tiles, about: by tile 8.5 + 900 E / T
 // (fan-out 1,500, 20,000 neurons on 157 tiles: 9.5 at 300 spikes, 21.9 at
 // 1,500, 45 at 4,000; 60,000 on 235: 9.5, 15.1, 28.8), through pages 14 + 4.3 E,
 // or 1.6 E where only one of several delays is filed (20,000: 39.3 at 4,000;
-// one delay of 20 16.4 at 1,500, 23.1 at 4,000; 60,000 23.3 at 4,000).
+// one delay of 20 16.4 at 1,500, 23.1 at 4,000; 60,000 23.3 at 4,000).  Not on
+// networks that count as direct: those use no scratch, and their callers need
+// not order such calls.
 bool binned_pays(const spk_net *net, uint64_t n_spikes, uint32_t delay)
 {
-    if (!net->ring || !net->compact) return false;
+    if (!ring_binned(net) || !net->compact) return false;
     const Tiling &tl = net->tl;
     const double E = 1e-6 * (double)n_spikes * (double)net->nnz / (double)net->n;
     const double T = (double)((net->n + tl.W - 1) / tl.W);
@@ -2212,11 +2226,7 @@ spk_status spk_stats(spk_net *net, spk_stats_t *out)
     st.bytes_per_synapse = net->proc ? 0.0 : net->compact ? 4.0 : 8.0;
     st.tile_width = net->ring ? net->rtl.W : net->tl.W;
     st.tiles = net->ring ? net->rtl.T : net->tl.T;
-    // (the resident kernel files events by arrival step right after their
-    // spike, as binned delivery does; with one delay of one step, or where
-    // direct delivery was asked for, a tile reads the due rows)
-    const bool filed = net->ring && net->P.delivery != SPK_DELIVERY_DIRECT && net->dmax > 1;
-    st.delivery = net->direct && !filed ? SPK_DELIVERY_DIRECT : SPK_DELIVERY_BINNED;
+    st.delivery = net->direct && !ring_binned(net) ? SPK_DELIVERY_DIRECT : SPK_DELIVERY_BINNED;
     st.page_cap = net->page_cap;
     st.step_mode = net->persistent ? SPK_STEP_PERSISTENT : SPK_STEP_GRAPH;
     st.batch_steps = net->persistent && (!net->direct || net->ring) ? net->run_D : 1u;

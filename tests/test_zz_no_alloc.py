@@ -83,7 +83,8 @@ RESIDENT = [  # parameters, spikes: lists that resident networks deliver by tile
     (lambda: I.scaled(4, 20_000, k_out=1500), (300, 4000)),
     (lambda: I.scaled(2, 6000, k_in_exc=800, k_in_inh=200), (50, 4000)),
     (lambda: I.config(0, n=4000, p=0.25, delay_max=3), (50, 2000)),
-    (lambda: I.config(0, n=1000, p=0.5), (10, 1000, 20_000)),  # (the last: IDs repeated, pages overflow)
+    (lambda: I.config(0, n=1000, p=0.5, delay_max=2), (10, 1000, 20_000)),  # (the last: IDs repeated, pages overflow)
+    (lambda: I.config(0, n=1000, p=0.5), (10, 1000, 20_000)),  # (direct: by tile whatever the list)
     (lambda: I.scaled(4, 131_072, k_out=100, delay_max=4), (1000, 131_072)),
 ]
 
