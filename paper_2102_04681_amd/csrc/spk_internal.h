@@ -293,7 +293,8 @@ struct RunArgs {
 // Resident step kernel (spk_ring.hip): one workgroup per tile, the inputs of
 // every pending arrival step in LDS.
 constexpr uint32_t kRingBytes = 96u << 10;   // LDS for the pending inputs of a tile
-constexpr uint32_t kRingBytes1 = 120u << 10; // ... of a network of one tile
+constexpr uint32_t kRingBytes1 = 120u << 10; // ... of a network of one tile, of at most kRingW1 neurons
+constexpr uint32_t kRingW1 = 2048;           // (the kernel for one tile; a wider one runs as several do)
 constexpr uint32_t kRingMaxT = 256;          // tiles
 // 8-byte words between mailboxes: a 128-byte line each (4 KB apart, as the
 // tile progress words, or packed by wave was slower: 250,000 neurons 9.3 / 8.8

@@ -866,6 +866,7 @@ hipError_t launch_ring_t(const RingArgs &ra, hipStream_t s)
 {
     const uint32_t nr = (ra.s.tl.W + kRT - 1) / kRT;
     if (ra.Tn == 1) {
+        static_assert(kRingW1 == 2 * kRT, "the kernel for one tile holds two neurons per thread");
         if (nr <= 1) return launch_ring_k<FIXED, CMP, CNT, false, 1>(ra, s);
         if (nr <= 2) return launch_ring_k<FIXED, CMP, CNT, false, 2>(ra, s);
     }
@@ -891,7 +892,7 @@ bool ring_supported(const RingArgs &ra)
     if (ra.counts && !a.compact) return false;
     if (!ra.counts && a.lists > 1) return false;  // (deliveries per step are counted from the event counts)
     if (a.compact ? !a.syn32 : !a.syn) return false;
-    return (uint64_t)a.pslots * tl.W * ring_acc_bytes(a.m.fixed, ra.counts) <= (ra.Tn == 1 ? kRingBytes1 : kRingBytes);
+    return (uint64_t)a.pslots * tl.W * ring_acc_bytes(a.m.fixed, ra.counts) <= (ra.Tn == 1 && tl.W <= kRingW1 ? kRingBytes1 : kRingBytes);
 }
 
 hipError_t launch_ring(const RingArgs &ra, hipStream_t s)

@@ -682,7 +682,7 @@ void plan_ring(spk_net *net, uint64_t nnz_expected, const uint64_t *in_max)
     const uint64_t nnz = nnz_expected;
     const bool fixed_cap = std::getenv("SPK_TILES_PER_XCD") != nullptr;
     auto fits = [&](uint32_t W) {
-        return (uint64_t)net->dmax * W * acc <= (W >= net->n ? kRingBytes1 : kRingBytes);
+        return (uint64_t)net->dmax * W * acc <= (W >= net->n && W <= kRingW1 ? kRingBytes1 : kRingBytes);
     };
     auto tiles = [&](uint32_t W) { return (net->n + W - 1) / W; };
     const bool source = P.neuron_kind == SPK_SOURCE;

@@ -136,6 +136,23 @@ def test_resident_kernel_tile_width(spk, mk, width):
     assert np.array_equal(a.debug_deliver(spikes).view(np.uint32), b.debug_deliver(spikes).view(np.uint32))
 
 
+@pytest.mark.parametrize("width,n,dmax,resident", [(4096, 3000, 6, True), (4096, 3000, 7, False), (8192, 7000, 3, True),
+                                                   (8192, 7000, 4, False), (2048, 2000, 15, True), (2048, 2000, 16, False),
+                                                   (64, 16_384, 5, True), (64, 16_385, 5, False)])
+def test_resident_kernel_widths_asked_for(spk, width, n, dmax, resident, monkeypatch):
+    # one tile wider than 2,048 neurons has the room of several, a narrower one
+    # more; at most 256 tiles
+    cfg, T = I.scaled(4, n, k_out=60, delay_max=dmax), 40
+    monkeypatch.setenv("SPK_RING", str(width))
+    a, b = spk.Net(cfg, max_steps=T), spk.Net(dict(cfg, step_mode=1), max_steps=T)
+    assert (a.stats()["page_cap"] == 0 and a.stats()["tile_width"] == width) == resident
+    for g in (a, b):
+        g.step(11)
+        g.step(T - 11)
+    assert a.spike_counts().sum() > 0
+    _same(_records(a, raster=False), _records(b, raster=False), "width")
+
+
 def test_resident_kernel_serves_one_delay_of_weights_per_synapse(spk):
     cfg = I.scaled(3, 9000, k_out=300, delay_min=2, delay_max=2)
     a, b = spk.Net(cfg, max_steps=50), spk.Net(dict(cfg, step_mode=1), max_steps=50)
